@@ -318,11 +318,10 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   }
   K.fp32 = P.precision == FRSG_FP32_MIXED ? 1 : 0;
   K.bf16 = (P.precision == FRSG_BF16_SPLIT && c->dim == 1) ? 1 : 0;
-  c->fused = !c->is_tri && fused2d_supported(K);
-  // the matrix-core kernel takes the BF16-split steps of the 2D quadrilateral path (and the
-  // FP64 ones where the VALU kernel does not apply)
-  c->quad = !c->is_tri && quad_mfma_supported(K) &&
-            (P.precision == FRSG_BF16_SPLIT || (P.precision == FRSG_FP64 && !c->fused));
+  // (the reduced precisions take the fused kernel's whole-tile instances only)
+  c->fused = !c->is_tri && fused2d_supported(K) && (P.precision == FRSG_FP64 || fused2d_whole(K));
+  // the matrix-core kernel takes the BF16-split steps of the 2D quadrilateral path
+  c->quad = !c->is_tri && quad_mfma_supported(K) && P.precision == FRSG_BF16_SPLIT;
   c->fused_tri = c->is_tri && tri_fused_supported(K);
   c->fused1d = c->dim == 1 && fr1d_supported(K);
   if (P.precision == FRSG_FP32_MIXED && !c->fused && !c->fused1d) {
@@ -370,7 +369,7 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   const size_t ntm = c->fused_tri ? (size_t)c->S * T.M * c->E * 3 * c->tri.nfp : 0;
   const bool adj = c->dim == 1 && c->S == 1;
   const size_t nadj_part = adj ? (size_t)std::max(adjoint_partials(K), adj1d_partials(K)) : 0;
-  const size_t ntr = c->quad ? quad_trace_count(P.nx, P.ny, T.M) : c->fused ? fused2d_trace_count(P.nx, P.ny, T.M) : 0;
+  const size_t ntr = c->quad ? quad_trace_count(P.nx, P.ny, T.M) : c->fused ? fused2d_trace_count(P.nx, P.ny, T.M, n) : 0;
   const Tableau* tab_rk = tableau_of(P.integrator);
   const int nrk = tab_rk ? tab_rk->s : 0;
   L.sc = take(256);

@@ -292,6 +292,7 @@ struct FusedStage {
   double* k_out = nullptr;
 };
 bool fused2d_supported(const KParams& P);
+bool fused2d_whole(const KParams& P);  // p = 3 elements in whole tiles: every precision's instances exist
 
 // one stage of the matrix-core 2D Euler path on quadrilaterals (kernels_quad_mfma.hip)
 struct QuadStage {
@@ -317,7 +318,7 @@ hipError_t launch_quad_stage(const KParams& P, const QuadStage& S, hipStream_t s
 // modal face traces of a state on every tile boundary face
 hipError_t launch_quad_traces(const KParams& P, const double* u, double* tr, hipStream_t s);
 // doubles of one modal face-trace buffer of the fused 2D kernel
-size_t fused2d_trace_count(int nx, int ny, int M);
+size_t fused2d_trace_count(int nx, int ny, int M, int np1);
 hipError_t launch_fused_stage(const KParams& P, const FusedStage& S, hipStream_t s);
 hipError_t launch_fused_cfl(const KParams& P, const double* u, unsigned long long* lam, hipStream_t s);
 // sensor-gated filter and/or limiter in place, with the fused kernel's tile layout

@@ -1,6 +1,6 @@
 // Fused FR-SG stage kernel for the 2D Euler equations on quadrilaterals with
-// p = 3 (4 x 4 Legendre-Gauss solution points), any gPC size M and random
-// node count NQ fixed at compile time.
+// p = 3 or p = 2 (N x N Legendre-Gauss solution points, N = 4 or 3), any gPC
+// size M and random node count NQ fixed at compile time, on any mesh.
 //
 // One kernel per SSP-RK3 stage does the whole right-hand side (Sec. 2.1, Sec.
 // 3.2-3.5) and the stage epilogue, reading each input coefficient from HBM
@@ -53,6 +53,8 @@
 // Exchanges between elements of the tile go through LDS.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device_common.hpp"
 #include "internal.hpp"
 #include "quad_device.hpp"
@@ -99,8 +101,8 @@ constexpr int BLKS = 32 * TE;        // threads per stage workgroup
 constexpr int NHF = 2 * (TX + TY);   // element faces on the tile boundary
 // modal face traces of one tile: per boundary face slot (x-lo rows, x-hi rows,
 // y-lo columns, y-hi columns), variable, face point and mode
-template <int M>
-constexpr int TRACE_PER_TILE = NHF * 4 * NP * M;
+template <int M, int N>
+constexpr int TRACE_PER_TILE = NHF * 4 * N * M;
 #ifndef FRSG_FP32_WAVES
 #define FRSG_FP32_WAVES 2  // waves per SIMD the FP32 node loop is compiled for (3 spills)
 #endif
@@ -161,18 +163,40 @@ struct LaneOps {
   double rlx[4], rly[4], rrx[4], rry[4];  // rotated l(-1), l(+1) for x (row a) and y (row b)
 };
 
+// entry c of an N-vector of point weights, 0 on the padding of a 16-lane row (c >= N)
+template <int N>
+__device__ __forceinline__ double wpad(const double* w, int c) {
+  return (N == NP || c < N) ? w[N == NP ? c : min(c, N - 1)] : 0.0;
+}
+// entry (r, c) of an N x N point matrix, 0 on the padding
+template <int N>
+__device__ __forceinline__ double mpad(const double* m, int r, int c) {
+  if constexpr (N == NP) return m[r * NP + c];
+  else return (r < N && c < N) ? m[min(r, N - 1) * N + min(c, N - 1)] : 0.0;
+}
+template <int N>
+__device__ __forceinline__ void make_lane_ops(const KParams& P, int a, int b, LaneOps& L) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    L.rlx[k] = wpad<N>(P.tab.lL, (a + k) & 3);
+    L.rrx[k] = wpad<N>(P.tab.lR, (a + k) & 3);
+    L.rly[k] = wpad<N>(P.tab.lL, (b - k) & 3);
+    L.rry[k] = wpad<N>(P.tab.lR, (b - k) & 3);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // positivity limiter on one element (Sec. 4.3); o[i][k]: this lane's pair
 // ---------------------------------------------------------------------------
-template <int M, int NQ>
+template <int M, int NQ, int N>
 __device__ int limit_pair(const KParams& P, const double* __restrict__ PhiT, double (&o)[2][M], int h, int a, int b,
-                          const LaneOps& L, const double* cmax) {
+                          const LaneOps& L, const double* cmax, bool inside, bool point) {
   const double g = P.gamma;
   double rwx[4], rwy[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    rwx[k] = 0.5 * P.tab.w[(a + k) & 3];
-    rwy[k] = 0.5 * P.tab.w[(b - k) & 3];
+    rwx[k] = 0.5 * wpad<N>(P.tab.w, (a + k) & 3);
+    rwy[k] = 0.5 * wpad<N>(P.tab.w, (b - k) & 3);
   }
   // element x random mean: sum_j (w_a/2)(w_b/2) o(j, mode 0)
   double ub[4];
@@ -180,7 +204,7 @@ __device__ int limit_pair(const KParams& P, const double* __restrict__ PhiT, dou
   const double pb = euler_p(ub, g);
   const bool realizable = ub[0] > 0.0 && pb > 0.0 && isfinite(ub[0]) && isfinite(ub[1]) && isfinite(ub[2]) &&
                           isfinite(ub[3]);
-  if (!realizable && a == 0 && b == 0 && h == 0) atomicOr(P.status, kStatusNotRealizable);
+  if (!realizable && inside && a == 0 && b == 0 && h == 0) atomicOr(P.status, kStatusNotRealizable);
   const double eps = fmin(1e-8, fmin(ub[0], pb));
 
   // rigorous bounds: value(z) = mean + sum_{k>=1} c_k Phi_k(z), |Phi_k(z_q)| <= cmax_k
@@ -244,12 +268,12 @@ __device__ int limit_pair(const KParams& P, const double* __restrict__ PhiT, dou
   const bool t01 = test_pair(0, 1);
   const bool t23 = test_pair(2, 3);
   const bool t40 = test_pair(4, 0);
-  const bool ok = t01 && t23 && t40;
+  const bool ok = (t01 && t23 && t40) || !point;
   // element-wide decision
   double okd = ok ? 1.0 : 0.0;
   okd = ymin4(xmin4(okd));
   okd = fmin(okd, other_half(okd));
-  const bool need = realizable && okd < 0.5;
+  const bool need = realizable && inside && okd < 0.5;
   if (__ballot(need) == 0) return 0;
 
   // node-by-node test (all lanes of the wave take part)
@@ -280,6 +304,7 @@ __device__ int limit_pair(const KParams& P, const double* __restrict__ PhiT, dou
     rmin = fmin(rmin, T[0]);
     pmin = fmin(pmin, euler_p(T, g));
   }
+  if (!point) rmin = pmin = INFINITY;
   rmin = ymin4(xmin4(rmin));
   pmin = ymin4(xmin4(pmin));
   const bool on = need && (fmin(rmin, pmin) < eps);
@@ -307,6 +332,7 @@ __device__ int limit_pair(const KParams& P, const double* __restrict__ PhiT, dou
     check(ydot(L.rly, u2[0]), ydot(L.rly, u2[1]));
     check(ydot(L.rry, u2[0]), ydot(L.rry, u2[1]));
   }
+  if (!point) bmin = 1.0;
   double beta2 = ymin4(xmin4(bmin));
   beta2 = fmin(beta2, other_half(beta2));
   if (on) {
@@ -328,16 +354,17 @@ __device__ int limit_pair(const KParams& P, const double* __restrict__ PhiT, dou
 // ---------------------------------------------------------------------------
 // detector + modal filter on one element (Sec. 4.1, 4.2)
 // ---------------------------------------------------------------------------
-template <int M>
-__device__ int sensor_filter_pair(const KParams& P, double (&o)[2][M], int h, int a, int b, int j,
+template <int M, int N>
+__device__ int sensor_filter_pair(const KParams& P, double (&o)[2][M], int h, int a, int b, int jp,
                                   const double* lam) {
+  constexpr int NS = N * N;
   double vix[4], viy[4], vx[4], vy[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    vix[k] = P.tab.Vinv[a * NP + ((a + k) & 3)];
-    viy[k] = P.tab.Vinv[b * NP + ((b - k) & 3)];
-    vx[k] = P.tab.V[a * NP + ((a + k) & 3)];
-    vy[k] = P.tab.V[b * NP + ((b - k) & 3)];
+    vix[k] = mpad<N>(P.tab.Vinv, a, (a + k) & 3);
+    viy[k] = mpad<N>(P.tab.Vinv, b, (b - k) & 3);
+    vx[k] = mpad<N>(P.tab.V, a, (a + k) & 3);
+    vy[k] = mpad<N>(P.tab.V, b, (b - k) & 3);
   }
   // energies of the first variable's spatial-chaos modes (meaningful on the h = 0 row)
   double num = 0.0, den = 0.0;
@@ -345,7 +372,7 @@ __device__ int sensor_filter_pair(const KParams& P, double (&o)[2][M], int h, in
   for (int k = 0; k < M; ++k) {
     const double t = ydot(viy, xdot(vix, o[0][k]));
     const double e2 = t * t;
-    num += e2 * P.tab.shell[k * NSP + j];
+    num += e2 * P.tab.shell[k * NS + jp];  // t is 0 on padding lanes
     den += e2;
   }
   num = row_bcast0(ysum4(xsum4(num)));
@@ -361,7 +388,7 @@ __device__ int sensor_filter_pair(const KParams& P, double (&o)[2][M], int h, in
   for (int i = 0; i < 2; ++i) {
 #pragma unroll
     for (int k = 0; k < M; ++k) {
-      const double t = ydot(viy, xdot(vix, o[i][k])) * lam[k * NSP + j];
+      const double t = ydot(viy, xdot(vix, o[i][k])) * lam[k * NS + jp];
       const double back = ydot(vy, xdot(vx, t));
       if (flag) o[i][k] = back;
     }
@@ -373,13 +400,15 @@ __device__ int sensor_filter_pair(const KParams& P, double (&o)[2][M], int h, in
 // the stage kernel; R is the type of the node loop (nodal values, fluxes,
 // residuals, projection), the epilogue runs in FP64
 // ---------------------------------------------------------------------------
-template <int M, int NQ, typename R, int FLUX>
+template <int M, int NQ, typename R, int FLUX, int N, bool RAG>
 __global__ void __launch_bounds__(BLKS) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 8 ? 2 : FRSG_FP32_WAVES)))
 k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
                                                   const R* __restrict__ PhiT, const R* __restrict__ PWT,
                                                   const double* __restrict__ in, const double* __restrict__ uin,
                                                   double* out) {
   constexpr bool kFP64 = sizeof(R) == sizeof(double);
+  constexpr int NS = N * N;  // solution points; a 16-lane row holds 4 x 4, the rest is padding
+  static_assert(RAG || N == NP, "a padded row needs the masked instance");
   // per element and row h (node q0 or q1 of the pair in hand): nodal values at
   // the solution points, traces at the flux points (x-lo row i, x-hi row i,
   // y-lo column i, y-hi column i; two pairs in flight) and interface fluxes
@@ -400,7 +429,7 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
   auto& sT = lds.loop.sT;
   auto& sFs = lds.loop.sFs;
   auto& sH = lds.loop.sH;
-  __shared__ double sLam[M * NSP];
+  __shared__ double sLam[M * NS];
   constexpr int NQP = (NQ + 1) & ~1;  // rows padded to whole 16-byte pairs
   __shared__ __attribute__((aligned(16))) double sPhiK[M][NQP];  // chaos basis, mode-major
   __shared__ double sRed[BLKS / 64];
@@ -409,10 +438,10 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
   const int le = tid >> 5, h = (tid >> 4) & 1, j = tid & 15;
   const int a = j & 3, b = j >> 2;
   const int lx = le % TX, ly = le / TX;
-  const int ntx = P.nx / TX;
+  const int ntx = RAG ? (P.nx + TX - 1) / TX : P.nx / TX;
   // XCD-aware order: consecutive workgroups go to different XCDs, so give each
   // XCD a contiguous band of tiles (neighbouring halos then share its L2)
-  const int nty = P.ny / TY, ntiles = ntx * nty;
+  const int nty = RAG ? (P.ny + TY - 1) / TY : P.ny / TY, ntiles = ntx * nty;
   int tile = blockIdx.x;
   if (ntiles % 8 == 0) tile = (tile % 8) * (ntiles / 8) + tile / 8;
   // within that order, walk blocks of 8 x 8 tiles: the tiles resident on an XCD
@@ -427,14 +456,21 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
     tx = tile % ntx;
     ty = tile / ntx;
   }
-  const int ix = TX * tx + lx, iy = TY * ty + ly;
+  // the last tile of a row or column may be cut short (tnx x th elements); the lanes
+  // past the mesh, and those past the N x N points of an element, run along on a
+  // neighbouring element's or point's data and take no part in any result
+  const int tnx = RAG ? min(TX, P.nx - TX * tx) : TX, tny = RAG ? min(TY, P.ny - TY * ty) : TY;
+  const bool inside = !RAG || (lx < tnx && ly < tny);
+  const bool point = N == NP || (a < N && b < N);
+  const int ix = TX * tx + (RAG ? min(lx, tnx - 1) : lx), iy = TY * ty + (RAG ? min(ly, tny - 1) : ly);
+  const int jp = N == NP ? j : min(a, N - 1) + N * min(b, N - 1);  // point index in the state arrays
   const int e = iy * P.nx + ix;
-  const long EN = (long)P.E * NSP;
+  const long EN = (long)P.E * NS;
   const R g = (R)P.gamma;
   const double dt = (A.stage == 0) ? 0.0 : *P.dt;
 
   if (A.stage == 3) {
-    for (int i = tid; i < M * NSP; i += BLKS) {
+    for (int i = tid; i < M * NS; i += BLKS) {
       const double f = P.tab.filt[i];
       sLam[i] = (P.filter == FRSG_FILTER_EXP) ? exp(-P.alpha * dt * f) : f;
     }
@@ -451,7 +487,7 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
 
   // own coefficients: variables 2h, 2h+1 (the state is below 4 GiB, checked by the host)
   const unsigned sbytes = (unsigned)(4 * M * EN * (long)sizeof(double));
-  const unsigned voff = (unsigned)(((long)(2 * h) * M * EN + (long)e * NSP + j) * (long)sizeof(double));
+  const unsigned voff = (unsigned)(((long)(2 * h) * M * EN + (long)e * NS + jp) * (long)sizeof(double));
   auto soff = [&](int i, int k) { return (unsigned)(((long)i * M + k) * EN * (long)sizeof(double)); };
   // the input in FP64 for the epilogue's combination, and in the loop's type (the same
   // registers in FP64; the FP32 loop keeps both, 255 registers without spills)
@@ -473,14 +509,17 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
   const bool halo_thread = tid < NHF * NP * 4;
   double th[M];  // modal trace of this thread's neighbour variable at its face point
   {
-    const int hf = (tid >> 4) % NHF, hfp = (tid >> 2) & 3, hs = tid & 3;
+    const int hf = (tid >> 4) % NHF, hfp = N == NP ? (tid >> 2) & 3 : min((tid >> 2) & 3, N - 1), hs = tid & 3;
     int nix, niy;
     bool along_x, from_lo;  // from_lo: the face is the neighbour's lo face (trace at -1)
     if (hf < TY) { nix = TX * tx - 1; niy = TY * ty + hf; along_x = true; from_lo = false; }
-    else if (hf < 2 * TY) { nix = TX * tx + TX; niy = TY * ty + hf - TY; along_x = true; from_lo = true; }
+    else if (hf < 2 * TY) { nix = TX * tx + tnx; niy = TY * ty + hf - TY; along_x = true; from_lo = true; }
     else if (hf < 2 * TY + TX) { nix = TX * tx + hf - 2 * TY; niy = TY * ty - 1; along_x = false; from_lo = false; }
-    else { nix = TX * tx + hf - 2 * TY - TX; niy = TY * ty + TY; along_x = false; from_lo = true; }
+    else { nix = TX * tx + hf - 2 * TY - TX; niy = TY * ty + tny; along_x = false; from_lo = true; }
     bool valid = halo_thread;
+    if constexpr (RAG)  // rows and columns past the mesh have no neighbour
+      valid = valid && (along_x ? (hf < TY ? hf : hf - TY) < tny
+                                : (hf < 2 * TY + TX ? hf - 2 * TY : hf - 2 * TY - TX) < tnx);
     if (nix < 0) { if (P.bc[0] == FRSG_BC_PERIODIC) nix += P.nx; else valid = false; }
     if (nix >= P.nx) { if (P.bc[1] == FRSG_BC_PERIODIC) nix -= P.nx; else valid = false; }
     if (niy < 0) { if (P.bc[2] == FRSG_BC_PERIODIC) niy += P.ny; else valid = false; }
@@ -496,8 +535,8 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
                      : hf < 2 * TY + TX ? hf + TX
                      : hf - TX;
       const int nt = valid ? (niy / TY) * ntx + nix / TX : 0;
-      const auto rtr = state_rsrc(A.tr_in, (unsigned)((long)ntiles * TRACE_PER_TILE<M> * (long)sizeof(double)));
-      const unsigned to = (unsigned)(((long)nt * TRACE_PER_TILE<M> + ((slot * 4 + hs) * NP + hfp) * M) *
+      const auto rtr = state_rsrc(A.tr_in, (unsigned)((long)ntiles * TRACE_PER_TILE<M, N> * (long)sizeof(double)));
+      const unsigned to = (unsigned)(((long)nt * TRACE_PER_TILE<M, N> + ((slot * 4 + hs) * N + hfp) * M) *
                                      (long)sizeof(double));
       if (halo_thread) {  // uniform per wave
 #pragma unroll
@@ -505,24 +544,28 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
       }
     } else {
       const int ne = valid ? niy * P.nx + nix : 0;
-      double lw[NP];
+      double lw[N];
 #pragma unroll
-      for (int c = 0; c < NP; ++c) lw[c] = from_lo ? P.tab.lL[c] : P.tab.lR[c];
+      for (int c = 0; c < N; ++c) lw[c] = from_lo ? P.tab.lL[c] : P.tab.lR[c];
       const auto rh = state_rsrc(in, sbytes);
-      unsigned ho[NP];
+      unsigned ho[N];
 #pragma unroll
-      for (int c = 0; c < NP; ++c)
-        ho[c] = (unsigned)((((long)hs * M) * EN + (long)ne * NSP + (along_x ? c + NP * hfp : hfp + NP * c)) *
+      for (int c = 0; c < N; ++c)
+        ho[c] = (unsigned)((((long)hs * M) * EN + (long)ne * NS + (along_x ? c + N * hfp : hfp + N * c)) *
                            (long)sizeof(double));
       if (halo_thread) {  // uniform per wave
-        double hv[M][NP];
+        double hv[M][N];
 #pragma unroll
         for (int k = 0; k < M; ++k)
 #pragma unroll
-          for (int c = 0; c < NP; ++c) hv[k][c] = bload(rh, ho[c], soff(0, k));
+          for (int c = 0; c < N; ++c) hv[k][c] = bload(rh, ho[c], soff(0, k));
 #pragma unroll
-        for (int k = 0; k < M; ++k)
-          th[k] = lw[0] * hv[k][0] + lw[1] * hv[k][1] + lw[2] * hv[k][2] + lw[3] * hv[k][3];
+        for (int k = 0; k < M; ++k) {
+          double t = lw[0] * hv[k][0];
+#pragma unroll
+          for (int c = 1; c < N; ++c) t += lw[c] * hv[k][c];
+          th[k] = t;
+        }
       }
     }
   }
@@ -551,10 +594,11 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
   R dx[4], dy[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    dx[k] = (R)A.Dt[a * NP + ((a + k) & 3)];
-    dy[k] = (R)A.Dt[b * NP + ((b - k) & 3)];
+    dx[k] = (R)mpad<N>(A.Dt, a, (a + k) & 3);
+    dy[k] = (R)mpad<N>(A.Dt, b, (b - k) & 3);
   }
-  const R dhLa = (R)P.tab.dhL[a], dhRa = (R)P.tab.dhR[a], dhLb = (R)P.tab.dhL[b], dhRb = (R)P.tab.dhR[b];
+  const R dhLa = (R)wpad<N>(P.tab.dhL, a), dhRa = (R)wpad<N>(P.tab.dhR, a);
+  const R dhLb = (R)wpad<N>(P.tab.dhL, b), dhRb = (R)wpad<N>(P.tab.dhR, b);
   const R iJx = (R)(1.0 / P.Jx), iJy = (R)(1.0 / P.Jy);
 
   // face-point role: flux point j of this element, side = j >> 2 (x-lo, x-hi, y-lo, y-hi), i = j & 3
@@ -566,7 +610,7 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
     else if (ix == 0 && P.bc[0] != FRSG_BC_PERIODIC) boundary = true;
     else nbr_halo = ly;
   } else if (fside == 1) {
-    if (lx < TX - 1) nbr_le = le + 1;
+    if (lx < tnx - 1) nbr_le = le + 1;
     else if (ix == P.nx - 1 && P.bc[1] != FRSG_BC_PERIODIC) boundary = true;
     else nbr_halo = TY + ly;
   } else if (fside == 2) {
@@ -574,7 +618,7 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
     else if (iy == 0 && P.bc[2] != FRSG_BC_PERIODIC) boundary = true;
     else nbr_halo = 2 * TY + lx;
   } else {
-    if (ly < TY - 1) nbr_le = le + TX;
+    if (ly < tny - 1) nbr_le = le + TX;
     else if (iy == P.ny - 1 && P.bc[3] != FRSG_BC_PERIODIC) boundary = true;
     else nbr_halo = 2 * TY + TX + lx;
   }
@@ -591,10 +635,10 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
 
   // the line of solution points through flux point j and its Lagrange weights
   // (l(-1) on a lo side, l(+1) on a hi side)
-  int line[4];
-  R wl[4];
+  int line[N];
+  R wl[N];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
+  for (int c = 0; c < N; ++c) {
     line[c] = (fside < 2) ? c + NP * fi : fi + NP * c;
     wl[c] = (R)(lo_side ? P.tab.lL[c] : P.tab.lR[c]);
   }
@@ -664,7 +708,7 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
     {
       R T[4] = {R(0), R(0), R(0), R(0)};
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
+      for (int c = 0; c < N; ++c) {
         const Half2<R> x0 = sU[le][h][0][line[c]], x1 = sU[le][h][1][line[c]];
         T[0] += wl[c] * x0.x;
         T[1] += wl[c] * x0.y;
@@ -758,11 +802,14 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
   // projected residual of mode k of variable 2h + i, in FP64
   auto res = [&](int i, int k) { return (!kFP64 && k == 0) ? acc0[i] : (double)acc[i][k]; };
   const auto rout = state_rsrc(out, sbytes);
+  const bool own = inside && point;  // the lane's point belongs to the state
   if (A.stage == 0) {
+    if (own) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int k = 0; k < M; ++k) bstore(res(i, k), rout, voff, soff(i, k));
+        for (int k = 0; k < M; ++k) bstore(res(i, k), rout, voff, soff(i, k));
+    }
     return;
   }
   double o[2][M];
@@ -787,7 +834,7 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
 #pragma unroll
       for (int k = 0; k < M; ++k) {
         const double r = res(i, k);
-        bstore(r, rko, voff, soff(i, k));
+        if (own) bstore(r, rko, voff, soff(i, k));
         const double t = (A.ka_cur != 0.0) ? o[i][k] + A.ka_cur * r : o[i][k];
         o[i][k] = bload_stream(ru, voff, soff(i, k)) + dt * t;
       }
@@ -804,28 +851,24 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
 
   if (A.stage == 3) {
     int ff = 0;
-    if (P.filter != FRSG_FILTER_NONE) ff = sensor_filter_pair<M>(P, o, h, a, b, j, sLam);
-    if (tid % 32 == 0 && A.flag_filt) A.flag_filt[e] = (unsigned char)ff;
+    if (P.filter != FRSG_FILTER_NONE) ff = sensor_filter_pair<M, N>(P, o, h, a, b, jp, sLam);
+    if (tid % 32 == 0 && inside && A.flag_filt) A.flag_filt[e] = (unsigned char)ff;
   }
   if (P.limiter) {
     LaneOps L;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      L.rlx[k] = P.tab.lL[(a + k) & 3];
-      L.rrx[k] = P.tab.lR[(a + k) & 3];
-      L.rly[k] = P.tab.lL[(b - k) & 3];
-      L.rry[k] = P.tab.lR[(b - k) & 3];
-    }
-    const int lf = limit_pair<M, NQ>(P, PhiTd, o, h, a, b, L, A.cmax);
-    if (tid % 32 == 0 && A.flag_lim && (lf || !A.flag_or)) A.flag_lim[e] = (unsigned char)lf;
-  } else if (tid % 32 == 0 && A.flag_lim && !A.flag_or) {
+    make_lane_ops<N>(P, a, b, L);
+    const int lf = limit_pair<M, NQ, N>(P, PhiTd, o, h, a, b, L, A.cmax, inside, point);
+    if (tid % 32 == 0 && inside && A.flag_lim && (lf || !A.flag_or)) A.flag_lim[e] = (unsigned char)lf;
+  } else if (tid % 32 == 0 && inside && A.flag_lim && !A.flag_or) {
     A.flag_lim[e] = 0;
   }
 
+  if (own) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int k = 0; k < M; ++k) bstore(o[i][k], rout, voff, soff(i, k));
+      for (int k = 0; k < M; ++k) bstore(o[i][k], rout, voff, soff(i, k));
+  }
 
   // modal face traces of the new state on the tile's boundary faces, for the
   // next launch's neighbours: the same interpolation, in the same order, as
@@ -838,28 +881,32 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
       for (int k = 0; k < M; ++k) lds.sO[le][2 * h + i][j][k] = o[i][k];
     __syncthreads();
     const int tile_id = ty * ntx + tx;
-    const auto rtr = state_rsrc(A.tr_out, (unsigned)((long)ntiles * TRACE_PER_TILE<M> * (long)sizeof(double)));
-    const unsigned tbase = (unsigned)((long)tile_id * TRACE_PER_TILE<M> * (long)sizeof(double));
-    constexpr int NR = (TRACE_PER_TILE<M> + BLKS - 1) / BLKS;
+    constexpr int TPT = TRACE_PER_TILE<M, N>;
+    const auto rtr = state_rsrc(A.tr_out, (unsigned)((long)ntiles * TPT * (long)sizeof(double)));
+    const unsigned tbase = (unsigned)((long)tile_id * TPT * (long)sizeof(double));
+    constexpr int NR = (TPT + BLKS - 1) / BLKS;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      const int oi = tid + r * BLKS;  // ((slot * 4 + s) * NP + point) * M + mode
-      if (oi < TRACE_PER_TILE<M>) {
-        const int k = oi % M, fp = (oi / M) % NP, sv = (oi / (M * NP)) % 4, slot = oi / (M * NP * 4);
+      const int oi = tid + r * BLKS;  // ((slot * 4 + s) * N + point) * M + mode
+      if (oi < TPT) {
+        const int k = oi % M, fp = (oi / M) % N, sv = (oi / (M * N)) % 4, slot = oi / (M * N * 4);
         int ex, ey;
         bool ax, lo;
         if (slot < TY) { ex = 0; ey = slot; ax = true; lo = true; }
-        else if (slot < 2 * TY) { ex = TX - 1; ey = slot - TY; ax = true; lo = false; }
+        else if (slot < 2 * TY) { ex = tnx - 1; ey = slot - TY; ax = true; lo = false; }
         else if (slot < 2 * TY + TX) { ex = slot - 2 * TY; ey = 0; ax = false; lo = true; }
-        else { ex = slot - 2 * TY - TX; ey = TY - 1; ax = false; lo = false; }
+        else { ex = slot - 2 * TY - TX; ey = tny - 1; ax = false; lo = false; }
         const int el = ex + TX * ey;
-        double v[NP], w[NP];
+        double v[N], w[N];
 #pragma unroll
-        for (int c = 0; c < NP; ++c) {
+        for (int c = 0; c < N; ++c) {
           v[c] = lds.sO[el][sv][ax ? c + NP * fp : fp + NP * c][k];
           w[c] = lo ? P.tab.lL[c] : P.tab.lR[c];
         }
-        bstore(w[0] * v[0] + w[1] * v[1] + w[2] * v[2] + w[3] * v[3], rtr, tbase + (unsigned)(oi * sizeof(double)), 0u);
+        double t = w[0] * v[0];
+#pragma unroll
+        for (int c = 1; c < N; ++c) t += w[c] * v[c];
+        bstore(t, rtr, tbase + (unsigned)(oi * sizeof(double)), 0u);
       }
     }
   }
@@ -907,6 +954,7 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
       full4(h, a2[0], a2[1], U);
       rate = fmax(rate, node_rate(U));
     }
+    if (!own) rate = 0.0;
     for (int w = 32; w > 0; w >>= 1) rate = fmax(rate, __shfl_xor(rate, w));
     if ((tid & 63) == 0) sRed[tid >> 6] = rate;
     __syncthreads();
@@ -924,29 +972,34 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
 // in that order, in place.  Used where they are not fused into a stage (the
 // tableau integrators, fr_sg_limit).
 // ---------------------------------------------------------------------------
-template <int M, int NQ>
+template <int M, int NQ, int N, bool RAG>
 __global__ void __launch_bounds__(BLKS) __attribute__((amdgpu_waves_per_eu(2)))
 k_post2d(KParams P, const double* __restrict__ PhiTd, const double* __restrict__ cmax, double* u, int do_filter,
          int do_limit, unsigned char* flag_filt, unsigned char* flag_lim) {
-  __shared__ double sLam[M * NSP];
+  constexpr int NS = N * N;
+  __shared__ double sLam[M * NS];
   const int tid = threadIdx.x;
   const int le = tid >> 5, h = (tid >> 4) & 1, j = tid & 15;
   const int a = j & 3, b = j >> 2;
   const int lx = le % TX, ly = le / TX;
-  const int ntx = P.nx / TX;
+  const int ntx = RAG ? (P.nx + TX - 1) / TX : P.nx / TX;
   const int tx = blockIdx.x % ntx, ty = blockIdx.x / ntx;
-  const int e = (TY * ty + ly) * P.nx + TX * tx + lx;
-  const long EN = (long)P.E * NSP;
+  // lanes past the mesh or past the element's points as in the stage kernel
+  const bool inside = !RAG || (TX * tx + lx < P.nx && TY * ty + ly < P.ny);
+  const bool point = N == NP || (a < N && b < N);
+  const int ix = RAG ? min(TX * tx + lx, P.nx - 1) : TX * tx + lx, iy = RAG ? min(TY * ty + ly, P.ny - 1) : TY * ty + ly;
+  const int e = iy * P.nx + ix, jp = N == NP ? j : min(a, N - 1) + N * min(b, N - 1);
+  const long EN = (long)P.E * NS;
   if (do_filter) {
     const double dt = *P.dt;
-    for (int i = tid; i < M * NSP; i += BLKS) {
+    for (int i = tid; i < M * NS; i += BLKS) {
       const double f = P.tab.filt[i];
       sLam[i] = (P.filter == FRSG_FILTER_EXP) ? exp(-P.alpha * dt * f) : f;
     }
     __syncthreads();
   }
   const unsigned sbytes = (unsigned)(4 * M * EN * (long)sizeof(double));
-  const unsigned voff = (unsigned)(((long)(2 * h) * M * EN + (long)e * NSP + j) * (long)sizeof(double));
+  const unsigned voff = (unsigned)(((long)(2 * h) * M * EN + (long)e * NS + jp) * (long)sizeof(double));
   auto soff = [&](int i, int k) { return (unsigned)(((long)i * M + k) * EN * (long)sizeof(double)); };
   const auto ru = state_rsrc(u, sbytes);
   double o[2][M];
@@ -955,25 +1008,21 @@ k_post2d(KParams P, const double* __restrict__ PhiTd, const double* __restrict__
 #pragma unroll
     for (int k = 0; k < M; ++k) o[i][k] = bload_stream(ru, voff, soff(i, k));
   if (do_filter) {
-    const int ff = sensor_filter_pair<M>(P, o, h, a, b, j, sLam);
-    if (tid % 32 == 0 && flag_filt) flag_filt[e] = (unsigned char)ff;
+    const int ff = sensor_filter_pair<M, N>(P, o, h, a, b, jp, sLam);
+    if (tid % 32 == 0 && inside && flag_filt) flag_filt[e] = (unsigned char)ff;
   }
   if (do_limit) {
     LaneOps L;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      L.rlx[k] = P.tab.lL[(a + k) & 3];
-      L.rrx[k] = P.tab.lR[(a + k) & 3];
-      L.rly[k] = P.tab.lL[(b - k) & 3];
-      L.rry[k] = P.tab.lR[(b - k) & 3];
-    }
-    const int lf = limit_pair<M, NQ>(P, PhiTd, o, h, a, b, L, cmax);
-    if (tid % 32 == 0 && flag_lim) flag_lim[e] = (unsigned char)lf;
+    make_lane_ops<N>(P, a, b, L);
+    const int lf = limit_pair<M, NQ, N>(P, PhiTd, o, h, a, b, L, cmax, inside, point);
+    if (tid % 32 == 0 && inside && flag_lim) flag_lim[e] = (unsigned char)lf;
   }
+  if (inside && point) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int k = 0; k < M; ++k) bstore(o[i][k], ru, voff, soff(i, k));
+      for (int k = 0; k < M; ++k) bstore(o[i][k], ru, voff, soff(i, k));
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -984,7 +1033,7 @@ __global__ void __launch_bounds__(BLK) k_cfl2d(KParams P, const double* __restri
                                                unsigned long long* lam) {
   __shared__ double sRed[BLK / 64];
   const long t = blockIdx.x * (long)BLK + threadIdx.x;
-  const long EN = (long)P.E * NSP;
+  const long EN = (long)P.E * P.nsp;
   double rate = 0.0;
   if (t < EN) {
     double o[4][M];
@@ -1060,43 +1109,56 @@ static hipError_t launch_stage_t(const KParams& P, const FusedStage& S, hipStrea
   A.ka_cur = S.ka_cur;
   A.k_out = S.k_out;
   A.flag_or = S.tab;
-  const int ntiles = (P.nx / TX) * (P.ny / TY);
-  if (S.fp32) {
-    if (P.flux == FRSG_FLUX_HLL)
-      hipLaunchKernelGGL((k_stage2d<M, NQ, float, FRSG_FLUX_HLL>), dim3(ntiles), dim3(BLKS), 0, s, P, A, S.PhiT,
-                         S.PhiT32, S.PWT32, S.in, S.u, S.out);
-    else
-      hipLaunchKernelGGL((k_stage2d<M, NQ, float, FRSG_FLUX_RUSANOV>), dim3(ntiles), dim3(BLKS), 0, s, P, A, S.PhiT,
-                         S.PhiT32, S.PWT32, S.in, S.u, S.out);
-  } else {
-    if (P.flux == FRSG_FLUX_HLL)
-      hipLaunchKernelGGL((k_stage2d<M, NQ, double, FRSG_FLUX_HLL>), dim3(ntiles), dim3(BLKS), 0, s, P, A, S.PhiT,
-                         S.PhiT, S.PWT, S.in, S.u, S.out);
-    else
-      hipLaunchKernelGGL((k_stage2d<M, NQ, double, FRSG_FLUX_RUSANOV>), dim3(ntiles), dim3(BLKS), 0, s, P, A,
-                         S.PhiT, S.PhiT, S.PWT, S.in, S.u, S.out);
-  }
-  return hipGetLastError();
+  const int ntiles = ((P.nx + TX - 1) / TX) * ((P.ny + TY - 1) / TY);
+  // instances: whole tiles of 4 x 4 points in either precision; FP64 also on meshes
+  // that 4 x 2 tiles do not divide and with 3 x 3 points, with masked lanes (the
+  // whole-tile instance does not pay for their registers and branches).  Against the
+  // multi-pass kernels, which stream every nodal array through memory: 2.13 -> 0.27 ms
+  // per step at 101 x 51 elements, p = 3, 15 modes, and 2.09 -> 0.31 ms at 128 x 64, p = 2
+  // (where 7 of a row's 16 lanes idle).
+  const bool whole = P.nx % TX == 0 && P.ny % TY == 0;
+  auto go = [&](auto r_tag, auto flux_tag, auto n_tag, auto rag_tag) -> hipError_t {
+    using R = decltype(r_tag);
+    constexpr int FLUX = decltype(flux_tag)::value, N = decltype(n_tag)::value;
+    constexpr bool RAG = decltype(rag_tag)::value;
+    const R *phi, *pw;
+    if constexpr (sizeof(R) == sizeof(float)) phi = S.PhiT32, pw = S.PWT32;
+    else phi = S.PhiT, pw = S.PWT;
+    hipLaunchKernelGGL((k_stage2d<M, NQ, R, FLUX, N, RAG>), dim3(ntiles), dim3(BLKS), 0, s, P, A, S.PhiT, phi, pw, S.in,
+                       S.u, S.out);
+    return hipGetLastError();
+  };
+  auto with_flux = [&](auto flux_tag) -> hipError_t {
+    using N4 = std::integral_constant<int, NP>;
+    if (S.fp32) return (P.np1 == NP && whole) ? go(float{}, flux_tag, N4{}, std::false_type{}) : hipErrorInvalidValue;
+    if (P.np1 == 3) return go(double{}, flux_tag, std::integral_constant<int, 3>{}, std::true_type{});
+    return whole ? go(double{}, flux_tag, N4{}, std::false_type{}) : go(double{}, flux_tag, N4{}, std::true_type{});
+  };
+  return P.flux == FRSG_FLUX_HLL ? with_flux(std::integral_constant<int, FRSG_FLUX_HLL>{})
+                                 : with_flux(std::integral_constant<int, FRSG_FLUX_RUSANOV>{});
 }
 
 template <int M, int NQ>
 static hipError_t launch_cfl_t(const KParams& P, const double* u, unsigned long long* lam, hipStream_t s) {
   hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(1), 0, s, lam);
-  const long EN = (long)P.E * NSP;
+  const long EN = (long)P.E * P.nsp;
   hipLaunchKernelGGL((k_cfl2d<M, NQ>), dim3((unsigned)((EN + BLK - 1) / BLK)), dim3(BLK), 0, s, P, u, lam);
   return hipGetLastError();
 }
 
 #define FRSG_FUSED_SIZES(X) X(15, 25) X(10, 16) X(6, 9) X(3, 4) X(5, 5)
 
-size_t fused2d_trace_count(int nx, int ny, int M) {
-  return (size_t)(nx / TX) * (size_t)(ny / TY) * (size_t)(NHF * 4 * NP) * (size_t)M;
+size_t fused2d_trace_count(int nx, int ny, int M, int np1) {
+  return (size_t)((nx + TX - 1) / TX) * (size_t)((ny + TY - 1) / TY) * (size_t)(NHF * 4 * np1) * (size_t)M;
 }
 
+bool fused2d_whole(const KParams& P) { return P.np1 == NP && P.nx % TX == 0 && P.ny % TY == 0; }
+
 bool fused2d_supported(const KParams& P) {
-  if (P.eq != kEuler2 || P.np1 != 4 || P.nx % TX != 0 || P.ny % TY != 0) return false;
-  // raw buffer offsets are 32-bit: the state must stay below 4 GiB
-  if ((double)4 * P.M * P.E * NSP * sizeof(double) >= 4294967296.0) return false;
+  if (P.eq != kEuler2 || (P.np1 != 4 && P.np1 != 3)) return false;
+  // raw buffer offsets are 32-bit: the state and a face-trace buffer must stay below 4 GiB
+  if ((double)4 * P.M * P.E * P.nsp * sizeof(double) >= 4294967296.0) return false;
+  if ((double)fused2d_trace_count(P.nx, P.ny, P.M, P.np1) * sizeof(double) >= 4294967296.0) return false;
 #define X(MM, QQ) if (P.M == MM && P.Nq == QQ) return true;
   FRSG_FUSED_SIZES(X)
 #undef X
@@ -1113,9 +1175,14 @@ hipError_t launch_fused_stage(const KParams& P, const FusedStage& S, hipStream_t
 template <int M, int NQ>
 static hipError_t launch_post_t(const KParams& P, const double* PhiTd, const double* cmax, double* u, int do_filter,
                                 int do_limit, unsigned char* flag_filt, unsigned char* flag_lim, hipStream_t s) {
-  const int ntiles = (P.nx / TX) * (P.ny / TY);
-  hipLaunchKernelGGL((k_post2d<M, NQ>), dim3(ntiles), dim3(BLKS), 0, s, P, PhiTd, cmax, u, do_filter, do_limit,
-                     flag_filt, flag_lim);
+  const int ntiles = ((P.nx + TX - 1) / TX) * ((P.ny + TY - 1) / TY);
+#define FRSG_POST(NN, RAG)                                                                                           \
+  hipLaunchKernelGGL((k_post2d<M, NQ, NN, RAG>), dim3(ntiles), dim3(BLKS), 0, s, P, PhiTd, cmax, u, do_filter, do_limit, \
+                     flag_filt, flag_lim)
+  if (P.np1 == 3) FRSG_POST(3, true);
+  else if (P.nx % TX == 0 && P.ny % TY == 0) FRSG_POST(NP, false);
+  else FRSG_POST(NP, true);
+#undef FRSG_POST
   return hipGetLastError();
 }
 
