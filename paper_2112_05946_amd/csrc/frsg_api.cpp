@@ -320,8 +320,18 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   K.bf16 = (P.precision == FRSG_BF16_SPLIT && c->dim == 1) ? 1 : 0;
   // (the reduced precisions take the fused kernel's whole-tile instances only)
   c->fused = !c->is_tri && fused2d_supported(K) && (P.precision == FRSG_FP64 || fused2d_whole(K));
-  // the matrix-core kernel takes the BF16-split steps of the 2D quadrilateral path
-  c->quad = !c->is_tri && quad_mfma_supported(K) && P.precision == FRSG_BF16_SPLIT;
+  // the matrix-core kernel takes the BF16-split steps of the 2D quadrilateral path, and the
+  // FP64 SSP-RK3 steps of meshes whose 2 x 2 tiles make at most one workgroup per compute
+  // unit: there a launch lasts as long as one workgroup, and a wave with one element and the
+  // transforms on the matrix cores finishes sooner than the 32 lanes per element of the
+  // fused kernel (15 modes, 25 nodes: 24 us per stage against 42 at 14 x 8, 28 against 45 at
+  // 30 x 34 elements); from the second round of workgroups on the fused kernel wins (49
+  // against 45 us at 38 x 34), and with few modes the matrix tiles are mostly padding (6
+  // modes: no difference).
+  const bool one_round = (long)(K.nx / 2) * (K.ny / 2) <= 256;
+  c->quad = !c->is_tri && quad_mfma_supported(K) &&
+            (P.precision == FRSG_BF16_SPLIT ||
+             (P.precision == FRSG_FP64 && P.integrator == FRSG_SSPRK3 && K.M > 6 && one_round));
   c->fused_tri = c->is_tri && tri_fused_supported(K);
   c->fused1d = c->dim == 1 && fr1d_supported(K);
   if (P.precision == FRSG_FP32_MIXED && !c->fused && !c->fused1d) {
