@@ -311,6 +311,8 @@ fr_sg_status fr_sg_step(fr_sg_ctx* ctx, double* u, double dt, double* dt_used, u
  * FP64 of FR degree <= 3 whose elements fit one workgroup ((E + 2) N_q <=
  * 1024, its stage data within 64 KB of LDS) runs the SSP-RK3 steps of the
  * call in one launch of one workgroup, with the same per-element arithmetic.
+ * Other 1D steps take one launch each (FR degree <= 4, FP64 or FP32-mixed), in
+ * which the state moves between u and the workspace; it ends in u.
  * dt_used: device double[nsteps] or NULL; flags: device uint8[nsteps * 4 * E]
  * or NULL, laid out per step as in fr_sg_step. */
 fr_sg_status fr_sg_steps(fr_sg_ctx* ctx, double* u, int32_t nsteps, double* dt_used, uint8_t* flags);

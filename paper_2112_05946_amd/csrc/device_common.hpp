@@ -12,6 +12,19 @@ namespace frsg {
 
 enum : int { kAdvection = FRSG_ADVECTION, kBurgers = FRSG_BURGERS, kEuler1 = FRSG_EULER1D, kEuler2 = FRSG_EULER2D };
 
+// 1/x to the accuracy of the type: hardware estimate refined by Newton steps
+__device__ __forceinline__ double recip(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  double e = fma(-x, r, 1.0);
+  r = fma(r, e, r);
+  e = fma(-x, r, 1.0);
+  return fma(r, e, r);
+}
+__device__ __forceinline__ float recip(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(r, fmaf(-x, r, 1.0f), r);
+}
+
 template <int EQ>
 __host__ __device__ constexpr int nstate() {
   return EQ <= kBurgers ? 1 : (EQ == kEuler1 ? 3 : 4);

@@ -276,7 +276,7 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   c->tab_off.clear();
   if (c->dim == 2 && !c->is_tri) build_quad_fragments(c->T);
   for (const std::vector<double>* v : {&T.r, &T.w, &T.D, &T.lL, &T.lR, &T.dhL, &T.dhR, &T.V, &T.Vinv, &T.Phi, &T.PW,
-                                       &T.filt, &T.shell, &T.swts, &T.Dt, &T.cmax, &T.PhiT, &T.PWT, &T.qfrag}) {
+                                       &T.filt, &T.shell, &T.swts, &T.Dt, &T.cmax, &T.PhiT, &T.PWT, &T.qfrag, &T.PWB, &T.op1}) {
     c->tab_off.push_back(blob.size());
     blob.insert(blob.end(), v->begin(), v->end());
   }
@@ -334,6 +334,9 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
              (P.precision == FRSG_FP64 && P.integrator == FRSG_SSPRK3 && K.M > 6 && one_round));
   c->fused_tri = c->is_tri && tri_fused_supported(K);
   c->fused1d = c->dim == 1 && fr1d_supported(K);
+  const Tableau* tab_rk = tableau_of(P.integrator);
+  const int nrk = tab_rk ? tab_rk->s : 0;
+  c->step1d = c->fused1d && step1d_supported(K, tab_rk ? nrk : 3, tab_rk != nullptr);
   if (P.precision == FRSG_FP32_MIXED && !c->fused && !c->fused1d) {
     err = "FRSG_FP32_MIXED runs on the fused 1D path (FR degree <= 7, Nq <= 85, one block's LDS within "
           "64 KiB) and the fused 2D Euler path (FR degree 3, nx % 4 == 0, ny % 2 == 0, a compiled (M, Nq) pair)";
@@ -380,8 +383,7 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   const bool adj = c->dim == 1 && c->S == 1;
   const size_t nadj_part = adj ? (size_t)std::max(adjoint_partials(K), adj1d_partials(K)) : 0;
   const size_t ntr = c->quad ? quad_trace_count(P.nx, P.ny, T.M) : c->fused ? fused2d_trace_count(P.nx, P.ny, T.M, n) : 0;
-  const Tableau* tab_rk = tableau_of(P.integrator);
-  const int nrk = tab_rk ? tab_rk->s : 0;
+  const size_t nlam = c->dim == 1 ? (size_t)step1d_partials(K) : 0;
   L.sc = take(256);
   L.tab = take(blob.size() * sizeof(double));
   L.f32 = take(c->host_f32.size() * sizeof(float));
@@ -404,6 +406,8 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   L.nrk = nrk;
   L.tm0 = take(ntm * 8);
   L.tm1 = take(ntm * 8);
+  L.lam0 = take(nlam * 8);
+  L.lam1 = take(nlam * 8);
   L.adj = adj;
   L.has_tr = ntr > 0;
   L.has_tm = ntm > 0;
@@ -540,6 +544,8 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
   tab.PhiT = c->dPhiT;
   tab.PWT = c->dPWT;
   c->dfrag = b + off[18];
+  tab.PWB = b + off[19];
+  tab.op1 = b + off[20];
   if (c->fused) {
     c->dPhiT32 = (const float*)(ws + L.f32);
     c->dPWT32 = c->dPhiT32 + c->T.PhiT.size();
@@ -582,16 +588,14 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
     W.tr[0] = (double*)(ws + L.tr0);
     W.tr[1] = (double*)(ws + L.tr1);
   }
+  W.lam1d[0] = (double*)(ws + L.lam0);
+  W.lam1d[1] = (double*)(ws + L.lam1);
   W.bytes = L.total;
   K.dt = W.scal;
   K.lam_bits = (unsigned long long*)(W.scal + 1);
   K.status = (unsigned*)(W.scal + 2);  // scal[3] is the second CFL accumulator
-  // small 1D problems run the steps of an fr_sg_steps call in one launch of one
-  // workgroup, where the kernel instance needs no register spills
-  c->resident1d = c->fused1d && c->prob.integrator == FRSG_SSPRK3 &&
-                  launch_steps1d_resident(K, nullptr, nullptr, nullptr, 0, 0, nullptr, nullptr, nullptr, nullptr,
-                                          c->stream) == hipSuccess;
-  (void)hipGetLastError();  // a failed attribute query leaves nothing for a later launch check
+  // small 1D problems run the steps of an fr_sg_steps call in one launch of one workgroup
+  c->resident1d = c->step1d && c->prob.integrator == FRSG_SSPRK3 && fr1d_resident_fits(K);
   *out = c;
   return FRSG_OK;
 }
@@ -881,35 +885,77 @@ static fr_sg_status step_fused1d(fr_sg_ctx* ctx, double* u, double dt, double* d
   return FRSG_OK;
 }
 
+// A whole 1D step per launch (SSP-RK3 or a Butcher tableau of up to four stages).  The
+// launch does not run in place unless one workgroup covers the mesh, so the state moves
+// between u and w1, which an odd number of steps enters through a copy: taken by the CFL
+// pass, which reads u anyway, or by a launch of its own before a step at a fixed dt.
+// w1, w2: where the stage states of a single SSP-RK3 step go (or null).
+static fr_sg_status steps_whole1d(fr_sg_ctx* ctx, double* u, int nsteps, double dt, double* dt_used, uint8_t* flags,
+                                  double* w1 = nullptr, double* w2 = nullptr) {
+  const KParams& K = ctx->kp;
+  Workspace& W = ctx->ws;
+  hipStream_t s = ctx->stream;
+  const Tableau* tb = tableau_of(ctx->prob.integrator);
+  const double sb = state_bytes(ctx);
+  Step1D T;
+  T.stages = tb ? tb->s : 3;
+  T.tab = tb != nullptr;
+  if (tb)
+    for (int i = 0; i < tb->s; ++i)
+      for (int j = 0; j <= i; ++j) T.rows[i][j] = i == tb->s - 1 ? tb->b[j] : tb->A[i + 1][j];
+  T.limit = ctx->prob.limiter ? 1 : 0;
+  T.w1 = w1, T.w2 = w2;
+  const bool fixed = dt > 0.0, in_place = step1d_one_workgroup(K, T.stages, T.tab);
+  double* copy = (!in_place && nsteps % 2 == 1) ? W.w1 : nullptr;
+  fr_sg_status st;
+  if (!fixed) {
+    if ((st = timed(ctx, "cfl", sb, [&] { return launch_cfl1d_part(K, u, W.lam1d[0], copy, &T.lam, s); }))) return st;
+  } else if (copy) {
+    if ((st = timed(ctx, "copy", 2 * sb, [&] { return launch_copy_state(u, copy, (long)(sb / 8), s); }))) return st;
+  }
+  T.dt = fixed ? dt : 0.0;
+  T.in = copy ? copy : u;
+  for (int i = 0; i < nsteps; ++i) {
+    T.out = in_place ? u : (T.in == u ? W.w1 : u);
+    T.flags = flags ? flags + 4l * ctx->E * i : nullptr;
+    T.dt_used = dt_used ? dt_used + i : nullptr;
+    // the maxima of the result are read by the next step of this call only
+    T.lam_part = (!fixed && i + 1 < nsteps) ? W.lam1d[(i + 1) & 1] : nullptr;
+    Lam1d next;
+    // (the pass goes by the name of the step's first stage: it holds all of them)
+    if ((st = timed(ctx, "stage1", 2 * sb, [&] { return launch_step1d(K, T, &next, s); }))) return st;
+    T.in = T.out;
+    T.lam = next;
+  }
+  return FRSG_OK;
+}
+
 // the steps of an fr_sg_steps call on a small 1D problem: the CFL pass of u, then
-// every step in one launch of one workgroup (the fused 1D stage code, three
-// stages per step separated by workgroup barriers); the CFL maximum of the result
-// is left where the next call's first step finds it
+// every step in one launch of one workgroup
 static fr_sg_status steps_resident1d(fr_sg_ctx* ctx, double* u, int nsteps, double* dt_used, uint8_t* flags) {
   const KParams& K = ctx->kp;
   Workspace& W = ctx->ws;
   hipStream_t s = ctx->stream;
-  unsigned long long* lam[2] = {(unsigned long long*)(W.scal + 1), (unsigned long long*)(W.scal + 3)};
-  const int cur = ctx->lam_cur;
   const double sb = state_bytes(ctx);
   fr_sg_status st;
-  if ((st = timed(ctx, "cfl", sb, [&] { return launch_cfl1d(K, u, lam[cur], s); }))) return st;
+  Lam1d lam;
+  if ((st = timed(ctx, "cfl", sb, [&] { return launch_cfl1d_part(K, u, W.lam1d[0], nullptr, &lam, s); }))) return st;
   const char* name = fr1d_resident_lds_state(K) ? "steps_resident_lds" : "steps_resident";
   // at most kChunk steps per launch (a few tens of milliseconds), the CFL maximum
-  // handed from launch to launch through the two accumulators
+  // handed from launch to launch
   constexpr int kChunk = 4096;
-  int c = cur;
+  int c = 1;
   for (int done = 0; done < nsteps; done += kChunk) {
     const int n = std::min(kChunk, nsteps - done);
     if ((st = timed(ctx, name, 8 * sb * n, [&] {
-           return launch_steps1d_resident(K, u, W.w1, W.w2, n, ctx->prob.limiter ? 1 : 0,
+           return launch_steps1d_resident(K, u, n, ctx->prob.limiter ? 1 : 0,
                                           flags ? flags + 4l * ctx->E * done : nullptr,
-                                          dt_used ? dt_used + done : nullptr, lam[c], lam[c ^ 1], s);
+                                          dt_used ? dt_used + done : nullptr, lam, W.lam1d[c], s);
          })))
       return st;
+    lam.at = W.lam1d[c], lam.n = 1;
     c ^= 1;
   }
-  ctx->lam_cur = c;
   return FRSG_OK;
 }
 
@@ -1247,6 +1293,7 @@ static fr_sg_status check_step_args(fr_sg_ctx* ctx, double* u, double dt) {
 fr_sg_status fr_sg_step(fr_sg_ctx* ctx, double* u, double dt, double* dt_used, uint8_t* flags) {
   fr_sg_status st = check_step_args(ctx, u, dt);
   if (st != FRSG_OK) return st;
+  if (ctx->step1d) return steps_whole1d(ctx, u, 1, dt, dt_used, flags);
   if (ctx->prob.integrator != FRSG_SSPRK3)
     return ctx->fused1d ? step_rk_fused1d(ctx, u, dt, dt_used, flags, false)
            : ctx->fused ? step_rk_fused2d(ctx, u, dt, dt_used, flags, false)
@@ -1265,6 +1312,7 @@ fr_sg_status fr_sg_steps(fr_sg_ctx* ctx, double* u, int32_t nsteps, double* dt_u
     return FRSG_EINVAL;
   }
   if (ctx->resident1d && nsteps > 0) return steps_resident1d(ctx, u, nsteps, dt_used, flags);
+  if (ctx->step1d && nsteps > 0) return steps_whole1d(ctx, u, nsteps, 0.0, dt_used, flags);
   const long fl = 4l * ctx->E;
   for (int i = 0; i < nsteps; ++i) {
     double* dtu = dt_used ? dt_used + i : nullptr;
@@ -1412,6 +1460,7 @@ fr_sg_status fr_sg_step_stages(fr_sg_ctx* ctx, double* u, double dt, double* dt_
     ctx->err = "w1 and w2 must be distinct device state buffers, distinct from u";
     return FRSG_EINVAL;
   }
+  if (ctx->step1d) return steps_whole1d(ctx, u, 1, dt, dt_used, flags, w1, w2);
   return step_fused1d(ctx, u, dt, dt_used, flags, false, w1, w2);
 }
 

@@ -15,6 +15,7 @@ namespace frsg {
 constexpr int kMaxNp1 = 8;      // p <= 7
 constexpr int kMaxModes = 128;  // gPC modes
 constexpr int kMaxNodes = 256;  // random quadrature nodes
+constexpr int kProjBlock = 3;   // modes per projection task of the whole-step 1D kernel
 
 // device status bits (latched, cleared by fr_sg_sync)
 constexpr unsigned kStatusNonFinite = 1u;
@@ -42,6 +43,8 @@ struct HostTables {
   std::vector<double> Dt;                // D - h_L' l(-1)^T - h_R' l(+1)^T (np1 x np1)
   std::vector<double> cmax;              // [M]: max_q |Phi_k(z_q)|
   std::vector<double> PhiT, PWT;         // [Nq * M] node-major copies of Phi, PW
+  std::vector<double> op1;               // 1D point operators in one block (DevTab)
+  std::vector<double> PWB;               // PW by blocks of kProjBlock modes (DevTab)
   std::vector<double> qfrag;             // matrix-core operand tables (quadrilateral 2D path)
 };
 
@@ -127,6 +130,8 @@ struct DevTab {
   const double* cmax;  // [M] max over the random nodes of |Phi_k|
   const double* PhiT;  // [Nq][M] node-major copies of Phi and PW (one node's modes contiguous)
   const double* PWT;
+  const double* op1;   // 1D point operators in one block: lL, lR, dhL, dhR, mean weights, D, Vinv, V
+  const double* PWB;   // [ceil(M / kProjBlock)][Nq][kProjBlock] PW by blocks of modes, zeros past the last mode
 };
 
 // Everything a kernel needs about the problem, passed by value.
@@ -171,6 +176,7 @@ struct Workspace {
   // fused triangles: modal traces [S][M][E][3 nfp] of a stage input, two buffers used in turn
   double* Tm[2] = {nullptr, nullptr};
   double* scal = nullptr;  // scalars: dt, lam bits, status
+  double* lam1d[2] = {nullptr, nullptr};  // whole 1D steps: per-workgroup CFL maxima, two arrays in turn
   // adjoint (scalar 1D problems): stage adjoints, trace adjoints, partial sums
   double* avb = nullptr;   // adjoint of the unfiltered end-of-step state
   double* ab2 = nullptr;   // adjoint of w2
@@ -191,6 +197,7 @@ struct Layout {
   size_t w1 = 0, w2 = 0, un = 0, fn = 0, gn = 0, co = 0;
   size_t avb = 0, ab2 = 0, ab1 = 0, agt = 0, apt = 0;
   size_t tr0 = 0, tr1 = 0, tm0 = 0, tm1 = 0;
+  size_t lam0 = 0, lam1 = 0;
   size_t rk[kRkMaxTerms] = {0};
   int nrk = 0;
   bool adj = false, has_tr = false, has_tm = false;
@@ -237,6 +244,7 @@ struct fr_sg_ctx {
   bool quad = false;             // matrix-core 2D Euler stage kernel (FP64, BF16-split)
   const double* dfrag = nullptr; // its operand tables
   bool fused1d = false;          // fused 1D stage kernel
+  bool step1d = false;           // a whole 1D step in one launch
   bool resident1d = false;       // SSP-RK3 steps of a small 1D problem in one one-workgroup launch
   int lam_cur = 0;              // which CFL accumulator holds the maximum of the current state
   const double* lam_for = nullptr;  // state whose maximum the previous step recorded (fr_sg_steps)
@@ -400,17 +408,41 @@ hipError_t launch_stage1d_tab(const KParams& P, const double* in, const double* 
                               int dt_source, double dt_fixed, const unsigned long long* lam_in,
                               unsigned long long* lam_reset, double* dt_used);
 hipError_t launch_cfl1d(const KParams& P, const double* u, unsigned long long* lam, hipStream_t s);
+// whole 1D steps per launch (kernels_step1d.hip).  CFL maxima: n values at `at`, whose
+// maximum is that of a state
+struct Lam1d {
+  const double* at = nullptr;
+  int n = 0;
+};
+struct Step1D {
+  const double* in = nullptr;
+  double* out = nullptr;             // equal to in only where one workgroup covers the mesh
+  double *w1 = nullptr, *w2 = nullptr;  // SSP-RK3: stage states handed out (or null)
+  int stages = 3;
+  bool tab = false;                  // Butcher rows instead of SSP-RK3
+  double rows[4][4] = {};            // row i forms the state after right-hand side i, the last the result
+  int limit = 0;
+  unsigned char* flags = nullptr;    // [4][E] or null
+  double dt = 0.0;                   // > 0: fixed; else from lam
+  Lam1d lam;
+  double* lam_part = nullptr;        // where the result's maxima go (step1d_partials doubles), or null
+  double* dt_used = nullptr;
+};
+bool step1d_supported(const KParams& P, int stages, bool tab);
+bool step1d_one_workgroup(const KParams& P, int stages, bool tab);
+long step1d_partials(const KParams& P);  // doubles of one array of CFL maxima
+hipError_t launch_step1d(const KParams& P, const Step1D& T, Lam1d* lam_out, hipStream_t s);
+// CFL maxima of u into part; with copy the state goes there too
+hipError_t launch_cfl1d_part(const KParams& P, const double* u, double* part, double* copy, Lam1d* lam, hipStream_t s);
+hipError_t launch_copy_state(const double* a, double* b, long n, hipStream_t s);
 // nsteps SSP-RK3 steps (CFL time steps, limiter on every stage output when limit,
 // end-of-step filter and CFL maximum) of an FP64 1D problem whose elements fit one
-// workgroup, in one launch; lam_in holds the CFL maximum of u, lam_out receives
+// workgroup, in one launch; lam_in holds the CFL maxima of u, lam_out receives
 // that of the result.  flags [nsteps][4][E] and dt_used [nsteps] may be null.
-// With u == nullptr: hipSuccess when the problem fits and the instance runs
-// without register spills, launching nothing.
 bool fr1d_resident_fits(const KParams& P);
-bool fr1d_resident_lds_state(const KParams& P);  // the three states stay in LDS for the whole call
-hipError_t launch_steps1d_resident(const KParams& P, double* u, double* w1, double* w2, int nsteps, int limit,
-                                   unsigned char* flags, double* dt_used, const unsigned long long* lam_in,
-                                   unsigned long long* lam_out, hipStream_t s);
+bool fr1d_resident_lds_state(const KParams& P);  // the state takes little enough of the compute unit's LDS
+hipError_t launch_steps1d_resident(const KParams& P, double* u, int nsteps, int limit, unsigned char* flags,
+                                   double* dt_used, const Lam1d& lam_in, double* lam_out, hipStream_t s);
 
 // adjoint launchers (kernels_adjoint.hip)
 long adjoint_partials(const KParams& P);

@@ -2,8 +2,9 @@
 // Euler): one launch computes the whole right-hand side of a block of elements
 // (Sec. 2.1 chaos expansion and Galerkin projection, Sec. 3.2-3.4 flux
 // reconstruction with Lax-Friedrichs interface fluxes per random node) and the
-// SSP-RK3 stage combination.  The limiter and the detector-switched filter stay
-// separate element-wise passes.
+// SSP-RK3 stage combination.  It serves fr_sg_rhs, the BF16-split steps, the adjoint's stage
+// states, and the steps that the one-launch kernel (step1d.hpp) does not take: FR degree above
+// 4, FP32-mixed and six-stage tableaux, many nodes.
 //
 // A workgroup owns EB consecutive elements plus one neighbour on each side:
 //   1. the modal coefficients of the EB + 2 elements are staged in LDS
@@ -76,8 +77,7 @@ struct Stage1DArgs {
   int flag_or;                   // limiter flags OR-ed into flag_lim (set only where it acts)
   // time step: dt_source 0 reads *P.dt; 1 takes dt_fixed; 2 computes it from the
   // CFL accumulator lam_in.  With 1 or 2, workgroup 0 also stores it in *P.dt and
-  // dt_used, zeroes lam_reset and latches a non-finite or non-positive dt.  3 takes
-  // dt_fixed and leaves all of that to the caller.
+  // dt_used, zeroes lam_reset and latches a non-finite or non-positive dt.
   int dt_source;
   double dt_fixed;
   const unsigned long long* lam_in;
@@ -88,15 +88,15 @@ struct Stage1DArgs {
 // padded sizes of the matrix-core operands: rows of 16, nodes in blocks of 16
 __host__ __device__ inline int pad16(int x) { return (x + 15) & ~15; }
 
-// One stage over the elements of workgroup blk, run by BS threads.  Returns the
-// CFL maximum of the workgroup's output (every thread) when it is asked for
-// (end of step and cfl_out), else 0.
-template <int EQ, int N, typename R, int XF, int BS>
-__device__ __forceinline__ double stage1d_block(const KParams& P, const Stage1DArgs& A, int blk) {
-  // products fuse with the sum of the same expression only, so every kernel that
-  // runs this code (one launch per stage, or several steps in one launch) rounds
-  // alike whatever it knows of the arguments at compile time
+// One stage over the elements of a workgroup
+template <int EQ, int N, typename R, int XF>
+__global__ void __launch_bounds__(kBlock1) k_stage1d(KParams P, Stage1DArgs A) {
+  // products fuse with the sum of the same expression only, so that the kernel of a
+  // whole step (step1d.hpp) and this one round alike whatever each knows of its
+  // arguments at compile time
 #pragma clang fp contract(on)
+  constexpr int BS = kBlock1;
+  const int blk = blockIdx.x;
   constexpr int S = nstate<EQ>();
   constexpr int n = N;
   extern __shared__ double smem[];
@@ -285,8 +285,6 @@ __device__ __forceinline__ double stage1d_block(const KParams& P, const Stage1DA
     dt = 0.0;
   } else if (A.dt_source == 0) {
     dt = *P.dt;
-  } else if (A.dt_source == 3) {
-    dt = A.dt_fixed;  // checked and published by the caller
   } else {
     // dt = CFL dx / ((p+1) lambda_max) from the accumulated wave-speed maximum
     dt = A.dt_source == 1 ? A.dt_fixed
@@ -337,7 +335,7 @@ __device__ __forceinline__ double stage1d_block(const KParams& P, const Stage1DA
   auto state_index = [&](int sk, int le, int j) { return (long)sk * EN + (long)(e0 + le) * n + j; };
   auto combine = [&](int sk, int le, int j, double acc, double uv, double wv) {
     double v;
-    if (BS < 1024 && A.tab) {  // (the one-workgroup kernel runs SSP-RK3 stages only)
+    if (A.tab) {
       const long idx = state_index(sk, le, j);
       if (A.k_out) A.k_out[idx] = acc;
       double t = 0.0;
@@ -365,8 +363,7 @@ __device__ __forceinline__ double stage1d_block(const KParams& P, const Stage1DA
   } else {
     // thread (variable, block of KB modes, element, point): one pass over the
     // nodal residual feeds KB independent sums, each taking the nodes in order
-    // (so every KB gives the same sums; the one-workgroup kernel, at 128
-    // registers per lane, keeps one mode per thread)
+    // (so every KB gives the same sums)
     auto project = [&](auto kb_tag) {
       constexpr int KB = decltype(kb_tag)::value;
       const int nkb = (M + KB - 1) / KB;
@@ -411,9 +408,7 @@ __device__ __forceinline__ double stage1d_block(const KParams& P, const Stage1DA
     // the tasks to a second pass of the workgroup's threads (the Euler problem
     // with 11 modes and 8 elements per workgroup: 288 tasks of four modes, 192 of
     // six, for 256 threads)
-    if constexpr (BS >= 1024)
-      project(std::integral_constant<int, 1>{});
-    else if constexpr (S == 1)
+    if constexpr (S == 1)
       project(std::integral_constant<int, 4>{});
     else if (S * ((M + 3) / 4) * ospan > BS && S * ((M + 5) / 6) * ospan <= BS)
       project(std::integral_constant<int, 6>{});
@@ -422,7 +417,7 @@ __device__ __forceinline__ double stage1d_block(const KParams& P, const Stage1DA
   }
   if (A.clear_flags)
     for (int it = tid; it < nloc; it += BS) A.clear_flags[e0 + it] = 0;
-  if (!epi) return 0.0;
+  if (!epi) return;
   __syncthreads();
 
   // 5. element epilogue: thread (owned element le, node q); per-(element, node)
@@ -642,7 +637,6 @@ __device__ __forceinline__ double stage1d_block(const KParams& P, const Stage1DA
   }
 
   // 5c. CFL maximum of the output for the next step
-  double lam_out = 0.0;
   if (A.end_of_step && A.cfl_out) {
     __shared__ double sm[BS / 64];
     double rate = 0.0;
@@ -674,7 +668,7 @@ __device__ __forceinline__ double stage1d_block(const KParams& P, const Stage1DA
     for (int o = 32; o > 0; o >>= 1) rate = fmax(rate, __shfl_xor(rate, o));
     if ((tid & 63) == 0) sm[tid >> 6] = rate;
     __syncthreads();
-    lam_out = sm[0];
+    double lam_out = sm[0];
     for (int w = 1; w < BS / 64; ++w) lam_out = fmax(lam_out, sm[w]);
     if (tid == 0 && A.lam_next) atomicMax(A.lam_next, (unsigned long long)__double_as_longlong(lam_out));
   }
@@ -685,12 +679,6 @@ __device__ __forceinline__ double stage1d_block(const KParams& P, const Stage1DA
     const int le2 = rem / n, j = rem - le2 * n;
     A.out[(long)sk * EN + (long)(e0 + le2) * n + j] = sO[le2 * ncoef + sk * n + j];
   }
-  return lam_out;
-}
-
-template <int EQ, int N, typename R, int XF>
-__global__ void __launch_bounds__(kBlock1) k_stage1d(KParams P, Stage1DArgs A) {
-  stage1d_block<EQ, N, R, XF, kBlock1>(P, A, blockIdx.x);
 }
 
 
@@ -739,113 +727,6 @@ __global__ void __launch_bounds__(kBlock1) k_cfl1d(KParams P, const double* __re
 }
 
 __global__ void k_zero_lam(unsigned long long* lam) { *lam = 0ull; }
-
-// Several SSP-RK3 steps of a small 1D problem in one launch.  One workgroup of
-// kBlockRes threads covers every element ((E + 2) element slots x N_q nodes <=
-// kBlockRes) and runs the three stages of each step back to back with the
-// stage code of k_stage1d, the stages separated by workgroup barriers.  Where
-// they fit, the state and the two stage states live in LDS for the whole call
-// (u is read once at the start and written once at the end); otherwise a stage
-// writes its output to global memory and the next stage, on the same compute
-// unit, reads it after the barrier.  The CFL maximum of each step's output stays
-// in the workgroup and sets the next step's dt.  Per element the arithmetic, and
-// so the result, is that of the three launches per step.
-constexpr int kBlockRes = 1024;
-
-struct Resident1DArgs {
-  double* u;                         // state, advanced in place
-  double* w1;                        // first and second stage states (global variant)
-  double* w2;
-  int nsteps;
-  int limit;                         // positivity limiter on every stage output
-  unsigned char* flags;              // [nsteps][4][E] or null
-  double* dt_used;                   // [nsteps] or null
-  const unsigned long long* lam_in;  // CFL maximum of u on entry
-  unsigned long long* lam_out;       // CFL maximum of the final state
-  long lds_tab;                      // offset in doubles of the LDS copies of Phi and PW
-  long lds_state;                    // > 0: offset in doubles of the three states in LDS
-  long nstate;                       // doubles per state
-};
-
-template <int EQ, int N>
-__global__ void __launch_bounds__(kBlockRes) k_steps1d_resident(KParams P0, Resident1DArgs RA) {
-  extern __shared__ double smem_res[];
-  // the chaos tables are read with per-thread indices inside loops over the
-  // modes and nodes: one workgroup cannot hide their cache latency, so they are
-  // read from LDS copies
-  KParams P = P0;
-  {
-    double* sPhi = smem_res + RA.lds_tab;
-    double* sPW = sPhi + P.M * P.Nq;
-    for (int i = threadIdx.x; i < P.M * P.Nq; i += kBlockRes) {
-      sPhi[i] = P0.tab.Phi[i];
-      sPW[i] = P0.tab.PW[i];
-    }
-    P.tab.Phi = sPhi;
-    P.tab.PW = sPW;
-  }
-  double *u = RA.u, *w1 = RA.w1, *w2 = RA.w2;
-  if (RA.lds_state > 0) {
-    double* base = smem_res + RA.lds_state;
-    for (long i = threadIdx.x; i < RA.nstate; i += kBlockRes) base[i] = RA.u[i];
-    u = base;
-    w1 = base + RA.nstate;
-    w2 = base + 2 * RA.nstate;
-  }
-  __syncthreads();
-  // the steps' dt collect in LDS and go out kRing at a time: a global store from
-  // inside a stage would hold the next workgroup barrier until it completes
-  constexpr int kRing = 256;
-  __shared__ double sdt[kRing];
-  double lam = __longlong_as_double((long long)*RA.lam_in);
-  double dt = 0.0;
-  const long fl = 4l * P.E;
-  const bool clear = !RA.limit;
-  for (int step = 0; step < RA.nsteps; ++step) {
-    // the expression of the stage kernel's CFL time step
-    dt = P.cfl * P.dx / (P.np1 * lam);
-    if (threadIdx.x == 0) {
-      if (!(dt > 0.0) || !isfinite(dt)) atomicOr(P.status, kStatusNonFinite);
-      sdt[step % kRing] = dt;
-    }
-    unsigned char* f = RA.flags ? RA.flags + step * fl : nullptr;
-    for (int st = 0; st < 3; ++st) {
-      Stage1DArgs A{};
-      A.u = u;
-      A.EB = P.E;
-      A.limit = RA.limit;
-      A.dt_source = 3;
-      A.dt_fixed = dt;
-      unsigned char* fs = f ? f + (st == 2 ? 3 : st) * (long)P.E : nullptr;
-      A.clear_flags = clear ? fs : nullptr;
-      A.flag_lim = fs;
-      if (st == 0) {
-        A.in = u, A.w = u, A.out = w1, A.cu = 0.0, A.cw = 1.0;
-      } else if (st == 1) {
-        A.in = w1, A.w = w1, A.out = w2, A.cu = 0.75, A.cw = 0.25;
-      } else {
-        A.in = w2, A.w = w2, A.out = u, A.cu = 1.0 / 3.0, A.cw = 2.0 / 3.0;
-        A.end_of_step = 1;
-        A.cfl_out = 1;
-        A.flag_filt = f ? f + 2 * (long)P.E : nullptr;
-      }
-      const double r = stage1d_block<EQ, N, double, 0, kBlockRes>(P, A, 0);
-      if (st == 2) lam = r;
-      __syncthreads();
-    }
-    if (step % kRing == kRing - 1 || step == RA.nsteps - 1) {
-      const int first = step - step % kRing;
-      if (RA.dt_used && (int)threadIdx.x <= step - first) RA.dt_used[first + threadIdx.x] = sdt[threadIdx.x];
-      __syncthreads();
-    }
-  }
-  if (RA.lds_state > 0)
-    for (long i = threadIdx.x; i < RA.nstate; i += kBlockRes) RA.u[i] = u[i];
-  if (threadIdx.x == 0) {
-    if (RA.nsteps > 0) *P.dt = dt;
-    *RA.lam_out = (unsigned long long)__double_as_longlong(lam);
-  }
-}
 
 }  // namespace
 
@@ -957,68 +838,6 @@ static hipError_t go_stage1d(const KParams& P, Stage1DArgs A, hipStream_t s) {
     case kAdvection: return go(std::integral_constant<int, kAdvection>{});
     case kBurgers: return go(std::integral_constant<int, kBurgers>{});
     case kEuler1: return go(std::integral_constant<int, kEuler1>{});
-    default: return hipErrorInvalidValue;
-  }
-}
-
-// the one-workgroup multi-step kernel: FP64 scalar equations of FR degree <= 3
-// (at 1024 threads a lane has 128 registers; the Euler and higher-degree
-// instances would spill), every element and its neighbours in one workgroup, the
-// stage LDS plus the CFL reduction's within 64 KB; the three states join them in
-// LDS where that stays within 64 KB
-constexpr int kMaxNRes = 4;
-constexpr size_t kLdsRes = 64 * 1024;
-static size_t fr1d_state_bytes(const KParams& P) { return sizeof(double) * (size_t)P.S * P.M * P.np1 * P.E; }
-// stage LDS, the chaos tables' copies, the CFL reduction and the ring of time steps
-static size_t fr1d_resident_lds(const KParams& P) {
-  return fr1d_lds(P, P.E) + sizeof(double) * (2 * (size_t)P.M * P.Nq + kBlockRes / 64 + 256);
-}
-bool fr1d_resident_fits(const KParams& P) {
-  if (P.dim != 1 || P.fp32 || P.bf16 || P.eq == kEuler1 || P.np1 < 2 || P.np1 > kMaxNRes) return false;
-  if ((long)(P.E + 2) * P.Nq > kBlockRes) return false;
-  return fr1d_resident_lds(P) <= kLdsRes;
-}
-bool fr1d_resident_lds_state(const KParams& P) {
-  return fr1d_resident_fits(P) && fr1d_resident_lds(P) + 3 * fr1d_state_bytes(P) <= kLdsRes;
-}
-
-template <int EQ, int N>
-static hipError_t go_resident(const KParams& P, const Resident1DArgs& RA, size_t shmem, hipStream_t s,
-                              bool check_only) {
-  if (check_only) {
-    hipFuncAttributes fa;
-    const hipError_t e = hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(&k_steps1d_resident<EQ, N>));
-    if (e != hipSuccess) return e;
-    return fa.localSizeBytes == 0 ? hipSuccess : hipErrorInvalidValue;
-  }
-  hipLaunchKernelGGL((k_steps1d_resident<EQ, N>), dim3(1), dim3(kBlockRes), shmem, s, P, RA);
-  return hipGetLastError();
-}
-
-// with u == nullptr only checks that the instance for P runs without register
-// spills (hipErrorInvalidValue otherwise)
-hipError_t launch_steps1d_resident(const KParams& P, double* u, double* w1, double* w2, int nsteps, int limit,
-                                   unsigned char* flags, double* dt_used, const unsigned long long* lam_in,
-                                   unsigned long long* lam_out, hipStream_t s) {
-  if (!fr1d_resident_fits(P)) return hipErrorInvalidValue;
-  const bool check_only = u == nullptr;
-  const bool in_lds = fr1d_resident_lds_state(P);
-  const long stage = (long)(fr1d_lds(P, P.E) / sizeof(double)), tab = 2l * P.M * P.Nq;
-  const Resident1DArgs RA{u,      w1,     w2,      nsteps, limit, flags, dt_used, lam_in, lam_out, stage,
-                          in_lds ? stage + tab : 0l, (long)(fr1d_state_bytes(P) / sizeof(double))};
-  const size_t shmem = sizeof(double) * (stage + tab) + (in_lds ? 3 * fr1d_state_bytes(P) : 0);
-  auto go = [&](auto eq_tag) -> hipError_t {
-    constexpr int EQ = decltype(eq_tag)::value;
-    switch (P.np1) {
-      case 2: return go_resident<EQ, 2>(P, RA, shmem, s, check_only);
-      case 3: return go_resident<EQ, 3>(P, RA, shmem, s, check_only);
-      case 4: return go_resident<EQ, 4>(P, RA, shmem, s, check_only);
-      default: return hipErrorInvalidValue;
-    }
-  };
-  switch (P.eq) {
-    case kAdvection: return go(std::integral_constant<int, kAdvection>{});
-    case kBurgers: return go(std::integral_constant<int, kBurgers>{});
     default: return hipErrorInvalidValue;
   }
 }

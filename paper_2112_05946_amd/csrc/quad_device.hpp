@@ -32,18 +32,6 @@ __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
 }
 
-// 1/x to the accuracy of the type: hardware estimate refined by Newton steps
-__device__ __forceinline__ double recip(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
-}
-__device__ __forceinline__ float recip(float x) {
-  const float r = __builtin_amdgcn_rcpf(x);
-  return fmaf(r, fmaf(-x, r, 1.0f), r);
-}
 __device__ __forceinline__ double sqrt_t(double x) { return sqrt(x); }
 // FP32: a pressure the FP64 limiter kept at its small positive floor can round
 // below zero in FP32 arithmetic; under a square root it counts as zero
