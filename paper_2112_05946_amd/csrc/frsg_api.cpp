@@ -352,7 +352,7 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   c->host_tri.clear();
   if (c->is_tri) {
     const TriTables& R = c->tri;
-    for (const std::vector<double>* v : {&R.Dr, &R.Ds, &R.Lf, &R.lift, &R.geo, &R.V, &R.Vinv})
+    for (const std::vector<double>* v : {&R.Dr, &R.Ds, &R.Lf, &R.lift, &R.geo, &R.V, &R.Vinv, &R.rows})
       c->host_tri.insert(c->host_tri.end(), v->begin(), v->end());
   }
   // FP32 copies of the node-major chaos tables (fused 2D path)
@@ -562,6 +562,7 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
     K.tri_geo = K.tri_lift + R.lift.size();
     K.tri_V = K.tri_geo + R.geo.size();
     K.tri_Vinv = K.tri_V + R.V.size();
+    K.tri_rows = K.tri_Vinv + R.Vinv.size();
     K.tri_nbr = (const int*)(ws + L.nbr);
   }
   Workspace& W = c->ws;
@@ -717,7 +718,7 @@ fr_sg_status fr_sg_rhs(fr_sg_ctx* ctx, const double* u, double* dudt) {
 static fr_sg_status rhs_into(fr_sg_ctx* ctx, const double* u, double* dudt) {
   if (ctx->fused_tri)
     return timed(ctx, "stage_rhs", 2 * state_bytes(ctx), [&] {
-      return launch_stage_tri(ctx->kp, u, u, u, dudt, 0.0, 1.0, 1, ctx->ws.Tm[0], 0, nullptr, ctx->stream);
+      return launch_stage_tri(ctx->kp, u, u, dudt, 0.0, 1.0, 1, ctx->ws.Tm[0], 0, nullptr, ctx->stream);
     });
   if (ctx->quad) {
     fr_sg_status st = timed(ctx, "traces", 0.0, [&] { return launch_quad_traces(ctx->kp, u, ctx->ws.tr[0], ctx->stream); });
@@ -765,8 +766,8 @@ static fr_sg_status step_generic(fr_sg_ctx* ctx, double* u, double dt, double* d
     // u (chained: u is the previous step's result)
     if (cfl) {
       if ((st = timed(ctx, "cfl", sb, [&] { return launch_cfl_tri_modal(K, u, s); }))) return st;
-      FRSG_TRY_HIP(launch_dt(K, ctx->dim, nullptr, s), ctx);
     }
+    const TriDt tdt{cfl ? 1 : 0, dt_used};  // the first stage takes dt and publishes it
     const int c0 = chained ? ctx->tm_cur : 0, c1 = c0 ^ 1;
     double* T0 = W.Tm[c0];
     double* T1 = W.Tm[c1];
@@ -782,18 +783,17 @@ static fr_sg_status step_generic(fr_sg_ctx* ctx, double* u, double dt, double* d
     p3.filter = filt ? 1 : 0;
     p3.flag_filt = filt ? f2 : nullptr;
     if ((st = timed(ctx, "stage1", 2 * sb, [&] {
-           return launch_stage_tri(K, u, u, u, W.w1, 0.0, 1.0, 0, T0, chained ? 1 : 0, T1, s, p1);
+           return launch_stage_tri(K, u, u, W.w1, 0.0, 1.0, 0, T0, chained ? 1 : 0, T1, s, p1, tdt);
          })))
       return st;
     if ((st = timed(ctx, "stage2", 3 * sb,
-                    [&] { return launch_stage_tri(K, W.w1, u, W.w1, W.w2, 0.75, 0.25, 0, T1, 1, T0, s, p2); })))
+                    [&] { return launch_stage_tri(K, W.w1, u, W.w2, 0.75, 0.25, 0, T1, 1, T0, s, p2); })))
       return st;
     if ((st = timed(ctx, "stage3", 3 * sb, [&] {
-           return launch_stage_tri(K, W.w2, u, W.w2, u, 1.0 / 3.0, 2.0 / 3.0, 0, T0, 1, T1, s, p3);
+           return launch_stage_tri(K, W.w2, u, u, 1.0 / 3.0, 2.0 / 3.0, 0, T0, 1, T1, s, p3);
          })))
       return st;
     ctx->tm_cur = c1;
-    if (dt_used) FRSG_TRY_HIP(launch_copy_dt(K, dt_used, s), ctx);
     return FRSG_OK;
   }
   // stage 1: w1 = Lim(u + dt R(u)); the CFL maximum is taken in the same pass over u

@@ -92,12 +92,20 @@ constexpr int kTriGeo = 16;                                     // doubles of ge
 // unit outward normals (nx, ny) of faces 0..2, the factors (face length /
 // reference face length / det) of faces 0..2, inscribed-circle diameter
 enum : int { kGeoRx = 0, kGeoRy, kGeoSx, kGeoSy, kGeoDet, kGeoN0 = 5, kGeoSc0 = 11, kGeoDin = 14 };
+// fused triangle stage: elements per block, and the split of an element operator's rows over
+// the block's waves (4 elements x 4 nodes x 4 variables are the 64 columns of a wave)
+constexpr int kTriEPB = 4;
+constexpr int tri_row_groups(int p) { return (kTriEPB * 4 * 3 * (p + 1) + 63) / 64; }
+constexpr int tri_trace_rows(int p) { return (3 * (p + 1) + tri_row_groups(p) - 1) / tri_row_groups(p); }
+constexpr int tri_point_rows(int p) { return ((p + 1) * (p + 2) / 2 + tri_row_groups(p) - 1) / tri_row_groups(p); }
+
 struct TriTables {
   int p = 0, np = 0, nfp = 0;
   std::vector<double> r, s;        // solution points on the reference triangle
   std::vector<double> Dr, Ds;      // [np][np]: d l_i/dr, d l_i/ds at point j (row j)
   std::vector<double> Lf;          // [3 nfp][np]: l_i at the flux points, face-major
   std::vector<double> lift;        // [np][3 nfp]: divergence of the correction fields
+  std::vector<double> rows;        // the element operators by row groups (KParams::tri_rows)
   std::vector<double> mean_w;      // [np]: element mean = sum_j mean_w[j] u_j
   std::vector<double> geo;         // [E][kTriGeo]
   std::vector<int> nbr;            // [E][6]: neighbour element (or -1 - side), then neighbour face
@@ -155,6 +163,9 @@ struct KParams {
   const double* tri_Ds;
   const double* tri_Lf;    // [3 nfp][N_p]
   const double* tri_lift;  // [N_p][3 nfp]
+  // per row group (tri_row_groups): for each point j the group's rows of L, Dr~ and Ds~ at
+  // column j, then for each flux point the group's rows of the lifting; rows past the last are 0
+  const double* tri_rows;
   const double* tri_geo;   // [E][kTriGeo]
   const double* tri_V;     // [N_p][N_p] orthonormal modes at the solution points, and inverse
   const double* tri_Vinv;
@@ -365,14 +376,20 @@ struct TriPost {
   int filter = 0, limit = 0;
   unsigned char *flag_filt = nullptr, *flag_lim = nullptr;
 };
+// where a stage's time step comes from: the CFL maximum in P.lam_bits (the kernel then stores
+// it in P.dt), or P.dt; dt_used receives it (may be null)
+struct TriDt {
+  int from_lam = 0;
+  double* dt_used = nullptr;
+};
 // fused triangle stage (p = 1..4 and the (M, Nq) pairs of the fused 2D kernel): a trace pass
-// over `in` into Tm ([S][M][E][3 nfp]) unless traces_ready, then out = cu u + cw (w + dt R(in)),
+// over `in` into Tm ([E][3][M][S][nfp]) unless traces_ready, then out = cu u + cw (in + dt R(in)),
 // or R(in) with rhs_only; `post` on the output (not with rhs_only); with Tm_out the traces
 // of the final `out` go there
 bool tri_fused_supported(const KParams& P);
-hipError_t launch_stage_tri(const KParams& P, const double* in, const double* u, const double* w, double* out,
-                            double cu, double cw, int rhs_only, double* Tm, int traces_ready, double* Tm_out,
-                            hipStream_t s, const TriPost& post = TriPost());
+hipError_t launch_stage_tri(const KParams& P, const double* in, const double* u, double* out, double cu, double cw,
+                            int rhs_only, double* Tm, int traces_ready, double* Tm_out, hipStream_t s,
+                            const TriPost& post = TriPost(), const TriDt& tdt = TriDt());
 // positivity limiter on triangles with the fused lane layout (fused (p, M, N_q) set)
 hipError_t launch_limit_tri(const KParams& P, double* u, unsigned char* flags, hipStream_t s);
 // the sensor-gated filter and/or the limiter of `post` as a pass of its own (same set)

@@ -207,6 +207,28 @@ bool build_tri_tables(const fr_sg_problem& P, TriTables& T, std::string& err) {
         T.lift[j * nf + fk] = kRefFaceLen[f] / 4.0 * wq[k] * acc;
       }
     }
+  // derivative with the interpolated normal flux at the faces folded in (the correction
+  // subtracts it): (face length / reference length / det) F . n = nr Fr + ns Gs on every element
+  const double rt = std::sqrt(0.5), nr[3] = {0.0, rt, -1.0}, ns[3] = {-1.0, rt, 0.0};
+  std::vector<double> Drt = T.Dr, Dst = T.Ds;
+  for (int j = 0; j < n; ++j)
+    for (int i = 0; i < n; ++i)
+      for (int fk = 0; fk < nf; ++fk) {
+        Drt[j * n + i] -= T.lift[j * nf + fk] * nr[fk / T.nfp] * T.Lf[fk * n + i];
+        Dst[j * n + i] -= T.lift[j * nf + fk] * ns[fk / T.nfp] * T.Lf[fk * n + i];
+      }
+  const int rg = tri_row_groups(p), rt_ = tri_trace_rows(p), rd = tri_point_rows(p);
+  auto row = [](const std::vector<double>& A, int r, int nrow, int ncol, int c) { return r < nrow ? A[r * ncol + c] : 0.0; };
+  T.rows.clear();
+  for (int w = 0; w < rg; ++w) {
+    for (int j = 0; j < n; ++j) {
+      for (int r = 0; r < rt_; ++r) T.rows.push_back(row(T.Lf, w * rt_ + r, nf, n, j));
+      for (int r = 0; r < rd; ++r) T.rows.push_back(row(Drt, w * rd + r, n, n, j));
+      for (int r = 0; r < rd; ++r) T.rows.push_back(row(Dst, w * rd + r, n, n, j));
+    }
+    for (int m = 0; m < nf; ++m)
+      for (int r = 0; r < rd; ++r) T.rows.push_back(row(T.lift, w * rd + r, n, nf, m));
+  }
   // mode (0, 0) is first and equals 1: the element mean is its coefficient
   T.mean_w.assign(Vi.begin(), Vi.begin() + n);
   T.V = V;
