@@ -322,16 +322,15 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   c->fused = !c->is_tri && fused2d_supported(K) && (P.precision == FRSG_FP64 || fused2d_whole(K));
   // the matrix-core kernel takes the BF16-split steps of the 2D quadrilateral path, and the
   // FP64 SSP-RK3 steps of meshes whose 2 x 2 tiles make at most one workgroup per compute
-  // unit: there a launch lasts as long as one workgroup, and a wave with one element and the
-  // transforms on the matrix cores finishes sooner than the 32 lanes per element of the
-  // fused kernel (15 modes, 25 nodes: 24 us per stage against 42 at 14 x 8, 28 against 45 at
-  // 30 x 34 elements); from the second round of workgroups on the fused kernel wins (49
-  // against 45 us at 38 x 34), and with few modes the matrix tiles are mostly padding (6
-  // modes: no difference).
+  // unit: there a launch lasts as long as one workgroup, and the transforms on the matrix cores
+  // finish sooner (15 modes, 25 nodes, five steps: 0.36 ms against the wave kernel's 0.44 at
+  // 14 x 8, 0.42 against 0.49 at 30 x 34 elements); from the second round of workgroups on the wave
+  // kernel wins (0.57 against 0.73 at 38 x 34), and with fewer modes the matrix tiles are mostly
+  // padding (10 modes: 0.29 against 0.27 at 20 x 10).
   const bool one_round = (long)(K.nx / 2) * (K.ny / 2) <= 256;
   c->quad = !c->is_tri && quad_mfma_supported(K) &&
             (P.precision == FRSG_BF16_SPLIT ||
-             (P.precision == FRSG_FP64 && P.integrator == FRSG_SSPRK3 && K.M > 6 && one_round));
+             (P.precision == FRSG_FP64 && P.integrator == FRSG_SSPRK3 && quad_fp64_modes(K.M) && one_round));
   c->fused_tri = c->is_tri && tri_fused_supported(K);
   c->fused1d = c->dim == 1 && fr1d_supported(K);
   const Tableau* tab_rk = tableau_of(P.integrator);
@@ -382,7 +381,7 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   const size_t ntm = c->fused_tri ? (size_t)c->S * T.M * c->E * 3 * c->tri.nfp : 0;
   const bool adj = c->dim == 1 && c->S == 1;
   const size_t nadj_part = adj ? (size_t)std::max(adjoint_partials(K), adj1d_partials(K)) : 0;
-  const size_t ntr = c->quad ? quad_trace_count(P.nx, P.ny, T.M) : c->fused ? fused2d_trace_count(P.nx, P.ny, T.M, n) : 0;
+  const size_t ntr = c->quad ? quad_trace_count(P.nx, P.ny, T.M) : c->fused ? fused2d_trace_count(K, P.precision == FRSG_FP64) : 0;
   const size_t nlam = c->dim == 1 ? (size_t)step1d_partials(K) : 0;
   L.sc = take(256);
   L.tab = take(blob.size() * sizeof(double));
@@ -400,8 +399,6 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   L.ab1 = take(adj ? state * 8 : 0);
   L.agt = take(adj ? (size_t)T.Nq * c->E * 2 * 8 : 0);
   L.apt = take(nadj_part * 8);
-  L.tr0 = take(ntr * 8);
-  L.tr1 = take(ntr * 8);
   for (int i = 0; i < nrk; ++i) L.rk[i] = take(state * 8);
   L.nrk = nrk;
   L.tm0 = take(ntm * 8);
@@ -411,13 +408,19 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   L.adj = adj;
   L.has_tr = ntr > 0;
   L.has_tm = ntm > 0;
+  // the traces last: the static workspace takes a problem whose buffers for the larger of the two
+  // tiles fit, and runs it without them where they do not fit for its own
+  L.least = o + (c->fused && !c->quad ? 2 * align_up(fused2d_trace_count(K, false) * 8) : 0);
+  L.tr0 = take(ntr * 8);
+  L.tr1 = take(ntr * 8);
   L.total = o;
+  if (!c->fused || c->quad) L.least = L.total;
+  L.least = std::min(L.least, L.total);
   return FRSG_OK;
 }
 
-extern "C" {
-
-fr_sg_status fr_sg_workspace_size(const fr_sg_problem* problem, int64_t* bytes) {
+// workspace of a problem, and the least that init_with_workspace takes without check_device
+fr_sg_status frsg::workspace_sizes(const fr_sg_problem* problem, int64_t* bytes, int64_t* least) {
   if (!problem || !bytes) {
     g_init_error = "problem and bytes must not be NULL";
     return FRSG_EINVAL;
@@ -430,12 +433,20 @@ fr_sg_status fr_sg_workspace_size(const fr_sg_problem* problem, int64_t* bytes) 
   }
   std::string err;
   const fr_sg_status st = prepare(*problem, c, err);
-  if (st == FRSG_OK)
+  if (st == FRSG_OK) {
     *bytes = (int64_t)c->lay.total;
-  else
+    if (least) *least = (int64_t)c->lay.least;
+  } else {
     g_init_error = err;
+  }
   delete c;
   return st;
+}
+
+extern "C" {
+
+fr_sg_status fr_sg_workspace_size(const fr_sg_problem* problem, int64_t* bytes) {
+  return frsg::workspace_sizes(problem, bytes, nullptr);
 }
 
 fr_sg_status fr_sg_init(const fr_sg_problem* problem, void* hip_stream, void* workspace, int64_t workspace_bytes,
@@ -472,7 +483,7 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
     return st;
   }
   const Layout& L = c->lay;
-  if (!workspace || workspace_bytes < (int64_t)L.total || ((uintptr_t)workspace & 255u) != 0) {
+  if (!workspace || workspace_bytes < (int64_t)(check_device ? L.total : L.least) || ((uintptr_t)workspace & 255u) != 0) {
     g_init_error = "workspace must be a 256-byte aligned device buffer of at least " + std::to_string(L.total) +
                    " bytes (fr_sg_workspace_size)";
     delete c;
@@ -585,7 +596,7 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
     W.Tm[0] = (double*)(ws + L.tm0);
     W.Tm[1] = (double*)(ws + L.tm1);
   }
-  if (L.has_tr) {
+  if (L.has_tr && workspace_bytes >= (int64_t)L.total) {
     W.tr[0] = (double*)(ws + L.tr0);
     W.tr[1] = (double*)(ws + L.tr1);
   }

@@ -213,6 +213,7 @@ struct Layout {
   int nrk = 0;
   bool adj = false, has_tr = false, has_tm = false;
   size_t total = 0;
+  size_t least = 0;  // enough to run: without the face-trace buffers at the end where total exceeds it
 };
 
 }  // namespace frsg
@@ -275,6 +276,8 @@ namespace frsg {
 // fr_sg_init's work on a given device workspace (frsg_api.cpp), and the text that
 // fr_sg_last_error(NULL) reports after a failed init
 // (check_device: confirm that the caller's pointer is device memory)
+// sizes for fr_sg_workspace_size and for the static workspace (Layout::total, Layout::least)
+fr_sg_status workspace_sizes(const fr_sg_problem* problem, int64_t* bytes, int64_t* least);
 fr_sg_status init_with_workspace(const fr_sg_problem* problem, void* hip_stream, void* workspace,
                                  int64_t workspace_bytes, fr_sg_ctx** out, bool check_device);
 void set_init_error(const std::string& msg);
@@ -330,6 +333,7 @@ struct QuadStage {
   const double* tr_in;  // modal face traces of `in` on tile boundaries (required)
   double* tr_out;       // where to write those of `out` (may be null)
 };
+constexpr bool quad_fp64_modes(int M) { return M > 10; }  // modes with which FP64 steps may take it
 bool quad_mfma_supported(const KParams& P);
 // doubles of one modal face-trace buffer of the matrix-core path
 size_t quad_trace_count(int nx, int ny, int M);
@@ -337,8 +341,28 @@ hipError_t launch_quad_stage(const KParams& P, const QuadStage& S, hipStream_t s
 // modal face traces of a state on every tile boundary face
 hipError_t launch_quad_traces(const KParams& P, const double* u, double* tr, hipStream_t s);
 // doubles of one modal face-trace buffer of the fused 2D kernel
-size_t fused2d_trace_count(int nx, int ny, int M, int np1);
+size_t fused2d_trace_count(const KParams& P, bool fp64);
 hipError_t launch_fused_stage(const KParams& P, const FusedStage& S, hipStream_t s);
+// ... in FP64 with one element per wave (kernels_wave2d.hip), nodes in groups of four, or with two
+// variables per lane and nodes in pairs (the pair kernel, k_stage2d).  The pair kernel keeps
+// the node counts that a group of four pads by more than an eighth (6 modes, 9 nodes, 100 x 50
+// elements: 0.52 against 0.58 ms per five steps).  It has two workgroups of 8 elements per compute
+// unit: with half of that or less (256 workgroups) a SIMD has one wave of it, and the wave kernel
+// wins (64 x 32 elements: 15 modes 0.59 against 0.70 ms, 10 modes 0.35 against 0.40).  From there to
+// a full round of workgroups (512) the pair kernel's round ends sooner (80 x 40: 0.81 against
+// 0.89 ms).  Beyond it the wave kernel's smaller workgroups leave less of the last round empty
+// and overlap one another's loads and node loops, at the price of a tenth more instructions per
+// element: with 15 modes that pays while the rounds are few (1.38 against 1.49 ms at 112 x 56, 2.04
+// against 2.18 at 144 x 72, 3.26 against 3.30 at 192 x 96; 10.93 against 10.92 per ten steps at
+// 256 x 128), with 10 it does not (1.62 against 1.52 at 160 x 80).
+constexpr bool wave2d_nodes(int nq) { return 8 * (((nq + 3) & ~3) - nq) <= nq; }
+constexpr int kWaveTile = 2;  // workgroup of the wave kernel: 2 x 2 elements
+inline int wave2d_tiles(int nx, int ny) { return ((nx + kWaveTile - 1) / kWaveTile) * ((ny + kWaveTile - 1) / kWaveTile); }
+inline bool wave2d_chosen(const KParams& P) {
+  const long pair_blocks = (long)((P.nx + 3) / 4) * ((P.ny + 1) / 2);
+  return wave2d_nodes(P.Nq) && (pair_blocks <= 256 || (pair_blocks > 512 && pair_blocks <= 2560 && P.M > 10));
+}
+hipError_t launch_wave_stage(const KParams& P, const FusedStage& S, hipStream_t s);
 hipError_t launch_fused_cfl(const KParams& P, const double* u, unsigned long long* lam, hipStream_t s);
 // sensor-gated filter and/or limiter in place, with the fused kernel's tile layout
 hipError_t launch_fused_post(const KParams& P, const double* PhiTd, const double* cmax, double* u, int do_filter,

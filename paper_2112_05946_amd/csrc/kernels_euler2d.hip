@@ -47,6 +47,9 @@
 // face read the same FP32 trace; across tiles the neighbour's side comes from
 // its FP64 modal trace, so the two traces agree to FP32 rounding there.
 //
+// FP64 here serves the node counts and mesh sizes for which kernels_wave2d.hip (one variable per
+// lane) is slower; the rule and both sides' times stand at wave2d_chosen.
+//
 // Exchanges inside an element: the 16 threads of an (element, h) form one
 // 16-lane DPP row, quad_perm rotations move along x (a) and row_ror:4k along y
 // (b); the two rows of an element trade values with v_permlane16_swap.
@@ -58,6 +61,7 @@
 #include "device_common.hpp"
 #include "internal.hpp"
 #include "quad_device.hpp"
+#include "stage2d.hpp"
 
 namespace frsg {
 namespace {
@@ -65,44 +69,13 @@ namespace {
 using namespace quad;
 constexpr int BLK = 256;    // threads per workgroup of the element-wise kernels
 
-// ---------------------------------------------------------------------------
-// arguments
-// ---------------------------------------------------------------------------
-struct StageArgs {
-  double cu, cw;             // out = cu u + cw (in + dt R)
-  int stage;                 // 0: right-hand side only; 1, 2: limited stage output; 3: end of step
-  unsigned char* flag_lim;   // per element: limiter acted on the output (stages 1-3)
-  unsigned char* flag_filt;  // per element: filter acted (stage 3)
-  unsigned long long* lam_next;  // stage 3: CFL accumulator of the new state (may be null)
-  const double* Dt;          // 4 x 4 modified derivative matrix
-  const double* cmax;        // [M] max_q |Phi_k(z_q)|
-  const double* tr_in;       // modal face traces of the input, or null: interpolate from the neighbours
-  double* tr_out;            // modal face traces of the output (may be null)
-  // Butcher-row form (tab) instead of cu u + cw (in + dt R): out = u + dt (sum_m ka[m] kk[m]
-  // + ka_cur R) over the earlier stage right-hand sides with nonzero coefficients, in stage
-  // order, R last (skipped when ka_cur is 0); R is also stored in k_out (may be null)
-  int tab, nt;
-  const double* kk[kRkMaxTerms];
-  double ka[kRkMaxTerms];
-  double ka_cur;
-  double* k_out;
-  int flag_or;               // limiter flags OR-ed into flag_lim (set only where it acts)
-};
-
 // Lane layout of a workgroup (one TX x TY tile of elements, 32 threads per element):
 //   tid = 32 le + 16 h + j,  j = a + 4 b,  le = lx + TX ly;
 // lane (le, h, j) owns conserved variables 2h and 2h+1 at solution point j of
 // local element le.  The 16 lanes with equal (le, h) form one DPP row, the two
 // rows of an element are partners, and the 32 lanes of an element sit in one
 // wave.
-constexpr int TX = 4, TY = 2;
-constexpr int TE = TX * TY;          // elements per tile
 constexpr int BLKS = 32 * TE;        // threads per stage workgroup
-constexpr int NHF = 2 * (TX + TY);   // element faces on the tile boundary
-// modal face traces of one tile: per boundary face slot (x-lo rows, x-hi rows,
-// y-lo columns, y-hi columns), variable, face point and mode
-template <int M, int N>
-constexpr int TRACE_PER_TILE = NHF * 4 * N * M;
 #ifndef FRSG_FP32_WAVES
 #define FRSG_FP32_WAVES 2  // waves per SIMD the FP32 node loop is compiled for (3 spills)
 #endif
@@ -134,46 +107,10 @@ __device__ __forceinline__ void full4(int h, T v0, T v1, T* U) {
   U[3] = h ? v1 : o1;
 }
 
-// Exchange between the two 16-lane rows of each 32-lane half (v_permlane16_swap
-// of a and b): afterwards b in row 0 holds row 1's a and a in row 1 holds row
-// 0's b, while a in row 0 and b in row 1 keep their values.  Every lane of the
-// wave must be active.
-__device__ __forceinline__ void swap_rows_u32(unsigned& a, unsigned& b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-  a = r[0];
-  b = r[1];
-}
-__device__ __forceinline__ void swap_rows(float& a, float& b) {
-  unsigned x = __float_as_uint(a), y = __float_as_uint(b);
-  swap_rows_u32(x, y);
-  a = __uint_as_float(x);
-  b = __uint_as_float(y);
-}
-__device__ __forceinline__ void swap_rows(double& a, double& b) {
-  const unsigned long long x = (unsigned long long)__double_as_longlong(a);
-  const unsigned long long y = (unsigned long long)__double_as_longlong(b);
-  unsigned xl = (unsigned)x, xh = (unsigned)(x >> 32), yl = (unsigned)y, yh = (unsigned)(y >> 32);
-  swap_rows_u32(xl, yl);
-  swap_rows_u32(xh, yh);
-  a = __longlong_as_double((long long)(((unsigned long long)xh << 32) | xl));
-  b = __longlong_as_double((long long)(((unsigned long long)yh << 32) | yl));
-}
-
 struct LaneOps {
   double rlx[4], rly[4], rrx[4], rry[4];  // rotated l(-1), l(+1) for x (row a) and y (row b)
 };
 
-// entry c of an N-vector of point weights, 0 on the padding of a 16-lane row (c >= N)
-template <int N>
-__device__ __forceinline__ double wpad(const double* w, int c) {
-  return (N == NP || c < N) ? w[N == NP ? c : min(c, N - 1)] : 0.0;
-}
-// entry (r, c) of an N x N point matrix, 0 on the padding
-template <int N>
-__device__ __forceinline__ double mpad(const double* m, int r, int c) {
-  if constexpr (N == NP) return m[r * NP + c];
-  else return (r < N && c < N) ? m[min(r, N - 1) * N + min(c, N - 1)] : 0.0;
-}
 template <int N>
 __device__ __forceinline__ void make_lane_ops(const KParams& P, int a, int b, LaneOps& L) {
 #pragma unroll
@@ -597,9 +534,17 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
     dx[k] = (R)mpad<N>(A.Dt, a, (a + k) & 3);
     dy[k] = (R)mpad<N>(A.Dt, b, (b - k) & 3);
   }
-  const R dhLa = (R)wpad<N>(P.tab.dhL, a), dhRa = (R)wpad<N>(P.tab.dhR, a);
-  const R dhLb = (R)wpad<N>(P.tab.dhL, b), dhRb = (R)wpad<N>(P.tab.dhR, b);
+  R dhLa = (R)wpad<N>(P.tab.dhL, a), dhRa = (R)wpad<N>(P.tab.dhR, a);
+  R dhLb = (R)wpad<N>(P.tab.dhL, b), dhRb = (R)wpad<N>(P.tab.dhR, b);
   const R iJx = (R)(1.0 / P.Jx), iJy = (R)(1.0 / P.Jy);
+  if constexpr (kFP64) {  // scaled once: r += dx . F + dy . G and the faces' terms
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      dx[k] *= -iJx;
+      dy[k] *= -iJy;
+    }
+    dhLa *= -iJx, dhRa *= -iJx, dhLb *= -iJy, dhRb *= -iJy;
+  }
 
   // face-point role: flux point j of this element, side = j >> 2 (x-lo, x-hi, y-lo, y-hi), i = j & 3
   const int fside = j >> 2, fi = j & 3;
@@ -685,7 +630,7 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
     swap_rows(U[1], U[3]);
     sU[le][h][0][j] = Half2<R>{U[0], U[1]};
     sU[le][h][1][j] = Half2<R>{U[2], U[3]};
-    R F[4], G[4];
+    R F[4], G[4], r[4];
     {
       const R ir = recip(U[0]);
       const R p = (g - R(1)) * (U[3] - R(0.5) * (U[1] * U[1] + U[2] * U[2]) * ir);
@@ -698,6 +643,15 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
       G[1] = U[1] * vy;
       G[2] = U[2] * vy + p;
       G[3] = (U[3] + p) * vy;
+    }
+    if constexpr (kFP64) {
+      // the divergence now: four values instead of eight through the interface flux (without the
+      // barrier the compiler moves the sums behind it, with their rotated operands)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        r[s] = xdot(dx, F[s]) + ydot(dy, G[s]);
+        asm volatile("" : "+v"(r[s]));
+      }
     }
     // the nodal values of an element are written and read by the same wave
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -765,10 +719,10 @@ k_stage2d(KParams P, StageArgs A, const double* __restrict__ PhiTd,
       const Half2<R> fyl1 = sFs[le][h][1][8 + a], fyr1 = sFs[le][h][1][12 + a];
       const R fxl[4] = {fxl0.x, fxl0.y, fxl1.x, fxl1.y}, fxr[4] = {fxr0.x, fxr0.y, fxr1.x, fxr1.y};
       const R fyl[4] = {fyl0.x, fyl0.y, fyl1.x, fyl1.y}, fyr[4] = {fyr0.x, fyr0.y, fyr1.x, fyr1.y};
-      R r[4];
 #pragma unroll
       for (int s = 0; s < 4; ++s)
-        r[s] = -(xdot(dx, F[s]) + fxl[s] * dhLa + fxr[s] * dhRa) * iJx -
+        if constexpr (kFP64) r[s] += fxl[s] * dhLa + fxr[s] * dhRa + fyl[s] * dhLb + fyr[s] * dhRb;
+        else r[s] = -(xdot(dx, F[s]) + fxl[s] * dhLa + fxr[s] * dhRa) * iJx -
                (ydot(dy, G[s]) + fyl[s] * dhLb + fyr[s] * dhRb) * iJy;
       swap_rows(r[0], r[2]);
       swap_rows(r[1], r[3]);
@@ -1089,31 +1043,12 @@ __global__ void k_zero_u64(unsigned long long* p) { *p = 0ull; }
 // ---------------------------------------------------------------------------
 template <int M, int NQ>
 static hipError_t launch_stage_t(const KParams& P, const FusedStage& S, hipStream_t s) {
-  StageArgs A;
-  A.cu = S.cu;
-  A.cw = S.cw;
-  A.stage = S.stage;
-  A.flag_lim = S.flag_lim;
-  A.flag_filt = S.flag_filt;
-  A.lam_next = S.lam_next;
-  A.Dt = S.Dt;
-  A.cmax = S.cmax;
-  A.tr_in = S.tr_in;
-  A.tr_out = S.tr_out;
-  A.tab = S.tab;
-  A.nt = S.tab ? S.terms.n : 0;
-  for (int t = 0; t < kRkMaxTerms; ++t) {
-    A.kk[t] = t < A.nt ? S.terms.K[t] : nullptr;
-    A.ka[t] = t < A.nt ? S.terms.a[t] : 0.0;
-  }
-  A.ka_cur = S.ka_cur;
-  A.k_out = S.k_out;
-  A.flag_or = S.tab;
+  const StageArgs A = stage_args(S);
   const int ntiles = ((P.nx + TX - 1) / TX) * ((P.ny + TY - 1) / TY);
   // instances: whole tiles of 4 x 4 points in either precision; FP64 also on meshes
   // that 4 x 2 tiles do not divide and with 3 x 3 points, with masked lanes (the
   // whole-tile instance does not pay for their registers and branches).  Against the
-  // multi-pass kernels, which stream every nodal array through memory: 2.13 -> 0.27 ms
+  // multi-pass kernels, which stream every nodal array through memory: 2.13 -> 0.27 ms with this kernel
   // per step at 101 x 51 elements, p = 3, 15 modes, and 2.09 -> 0.31 ms at 128 x 64, p = 2
   // (where 7 of a row's 16 lanes idle).
   const bool whole = P.nx % TX == 0 && P.ny % TY == 0;
@@ -1146,10 +1081,11 @@ static hipError_t launch_cfl_t(const KParams& P, const double* u, unsigned long 
   return hipGetLastError();
 }
 
-#define FRSG_FUSED_SIZES(X) X(15, 25) X(10, 16) X(6, 9) X(3, 4) X(5, 5)
-
-size_t fused2d_trace_count(int nx, int ny, int M, int np1) {
-  return (size_t)((nx + TX - 1) / TX) * (size_t)((ny + TY - 1) / TY) * (size_t)(NHF * 4 * np1) * (size_t)M;
+// modal face traces of a state at the tiles' boundaries
+size_t fused2d_trace_count(const KParams& P, bool fp64) {
+  const size_t per_face = (size_t)4 * P.np1 * P.M;
+  if (fp64 && wave2d_chosen(P)) return (size_t)wave2d_tiles(P.nx, P.ny) * 4 * kWaveTile * per_face;
+  return (size_t)((P.nx + TX - 1) / TX) * (size_t)((P.ny + TY - 1) / TY) * NHF * per_face;
 }
 
 bool fused2d_whole(const KParams& P) { return P.np1 == NP && P.nx % TX == 0 && P.ny % TY == 0; }
@@ -1158,7 +1094,8 @@ bool fused2d_supported(const KParams& P) {
   if (P.eq != kEuler2 || (P.np1 != 4 && P.np1 != 3)) return false;
   // raw buffer offsets are 32-bit: the state and a face-trace buffer must stay below 4 GiB
   if ((double)4 * P.M * P.E * P.nsp * sizeof(double) >= 4294967296.0) return false;
-  if ((double)fused2d_trace_count(P.nx, P.ny, P.M, P.np1) * sizeof(double) >= 4294967296.0) return false;
+  for (const bool fp64 : {false, true})
+    if ((double)fused2d_trace_count(P, fp64) * sizeof(double) >= 4294967296.0) return false;
 #define X(MM, QQ) if (P.M == MM && P.Nq == QQ) return true;
   FRSG_FUSED_SIZES(X)
 #undef X
@@ -1166,6 +1103,7 @@ bool fused2d_supported(const KParams& P) {
 }
 
 hipError_t launch_fused_stage(const KParams& P, const FusedStage& S, hipStream_t s) {
+  if (!S.fp32 && wave2d_chosen(P)) return launch_wave_stage(P, S, s);
 #define X(MM, QQ) if (P.M == MM && P.Nq == QQ) return launch_stage_t<MM, QQ>(P, S, s);
   FRSG_FUSED_SIZES(X)
 #undef X

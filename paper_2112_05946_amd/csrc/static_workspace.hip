@@ -28,10 +28,10 @@ extern "C" fr_sg_status fr_sg_init_static(const fr_sg_problem* problem, void* hi
     return FRSG_EINVAL;
   }
   *out = nullptr;
-  int64_t need = 0;
-  const fr_sg_status st = fr_sg_workspace_size(problem, &need);  // validates; sets the error text
+  int64_t need = 0, least = 0;
+  const fr_sg_status st = frsg::workspace_sizes(problem, &need, &least);  // validates; sets the error text
   if (st != FRSG_OK) return st;
-  if (need > kStaticWorkspaceBytes) {
+  if (least > kStaticWorkspaceBytes) {
     frsg::set_init_error("problem needs a workspace of " + std::to_string(need) +
                          " bytes; the static workspace holds " + std::to_string(kStaticWorkspaceBytes) +
                          " (use fr_sg_init with a caller-allocated workspace)");
