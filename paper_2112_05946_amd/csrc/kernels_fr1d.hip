@@ -88,15 +88,16 @@ struct Stage1DArgs {
 // padded sizes of the matrix-core operands: rows of 16, nodes in blocks of 16
 __host__ __device__ inline int pad16(int x) { return (x + 15) & ~15; }
 
-// One stage over the elements of a workgroup
-template <int EQ, int N, typename R, int XF>
-__global__ void __launch_bounds__(kBlock1) k_stage1d(KParams P, Stage1DArgs A) {
+// One stage over the elements of workgroup blk, run by BS threads; the CFL maximum of its output
+// (every thread) when it is asked for.  (A function of its own, with the arguments by reference: in
+// the kernel's body the compiler keeps them all in scalar registers and spills a hundred, 9 % of
+// a bfloat16-split Sod step.)
+template <int EQ, int N, typename R, int XF, int BS>
+__device__ __forceinline__ double stage1d_block(const KParams& P, const Stage1DArgs& A, int blk) {
   // products fuse with the sum of the same expression only, so that the kernel of a
   // whole step (step1d.hpp) and this one round alike whatever each knows of its
   // arguments at compile time
 #pragma clang fp contract(on)
-  constexpr int BS = kBlock1;
-  const int blk = blockIdx.x;
   constexpr int S = nstate<EQ>();
   constexpr int n = N;
   extern __shared__ double smem[];
@@ -417,7 +418,8 @@ __global__ void __launch_bounds__(kBlock1) k_stage1d(KParams P, Stage1DArgs A) {
   }
   if (A.clear_flags)
     for (int it = tid; it < nloc; it += BS) A.clear_flags[e0 + it] = 0;
-  if (!epi) return;
+  if (!epi) return 0.0;
+  double lam_out = 0.0;
   __syncthreads();
 
   // 5. element epilogue: thread (owned element le, node q); per-(element, node)
@@ -668,7 +670,7 @@ __global__ void __launch_bounds__(kBlock1) k_stage1d(KParams P, Stage1DArgs A) {
     for (int o = 32; o > 0; o >>= 1) rate = fmax(rate, __shfl_xor(rate, o));
     if ((tid & 63) == 0) sm[tid >> 6] = rate;
     __syncthreads();
-    double lam_out = sm[0];
+    lam_out = sm[0];
     for (int w = 1; w < BS / 64; ++w) lam_out = fmax(lam_out, sm[w]);
     if (tid == 0 && A.lam_next) atomicMax(A.lam_next, (unsigned long long)__double_as_longlong(lam_out));
   }
@@ -679,8 +681,13 @@ __global__ void __launch_bounds__(kBlock1) k_stage1d(KParams P, Stage1DArgs A) {
     const int le2 = rem / n, j = rem - le2 * n;
     A.out[(long)sk * EN + (long)(e0 + le2) * n + j] = sO[le2 * ncoef + sk * n + j];
   }
+  return lam_out;
 }
 
+template <int EQ, int N, typename R, int XF>
+__global__ void __launch_bounds__(kBlock1) k_stage1d(KParams P, Stage1DArgs A) {
+  stage1d_block<EQ, N, R, XF, kBlock1>(P, A, blockIdx.x);
+}
 
 // CFL maximum of a 1D state: a workgroup stages the coefficients of 256 / Nq
 // elements in LDS; thread (element, node q) takes the maximum over the points
