@@ -176,6 +176,21 @@ __device__ __forceinline__ double pressure_root(const double* ub, const double* 
   return (b < 0.0) ? 2.0 * c / (-b + sq) : (-b - sq) / (2.0 * a);
 }
 
+// a stage's time step (StageDt), in scalar registers; the first thread of the grid publishes a new one
+__device__ __forceinline__ double stage_dt(const KParams& P, const StageDt& D) {
+  if (!D.lam) return *P.dt;
+  const double dt = P.cfl / (P.np1 * __longlong_as_double((long long)*D.lam));
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (!(dt > 0.0) || !isfinite(dt)) atomicOr(P.status, kStatusNonFinite);
+    *P.dt = dt;
+    if (D.dt_used) *D.dt_used = dt;
+    if (D.lam_reset) *D.lam_reset = 0ull;
+  }
+  const long long x = __double_as_longlong(dt);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)x), hi = __builtin_amdgcn_readfirstlane((int)(x >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // block-wide reductions over blockDim.x <= 256 threads (shared scratch of 256 doubles)
 __device__ __forceinline__ double block_reduce_min(double v, double* sm) {
   sm[threadIdx.x] = v;

@@ -288,6 +288,15 @@ struct RkTerms {
   double a[kRkMaxTerms];
   int n;
 };
+// Where a stage of the wave kernel has its time step from: P.dt, or (first stage of a CFL step) the
+// CFL maximum in lam; the kernel then publishes it in P.dt and dt_used (may be null) and clears lam_reset, the
+// accumulator of the step's last stage.  Launches of their own for that cost up to 10 us of a step
+// (100 x 50 elements, Bogacki-Shampine, flags cleared by the first stage too: 279 -> 270 us).
+struct StageDt {
+  const unsigned long long* lam = nullptr;
+  unsigned long long* lam_reset = nullptr;
+  double* dt_used = nullptr;
+};
 struct FusedStage {
   const double* in;
   const double* u;
@@ -307,11 +316,14 @@ struct FusedStage {
   const double* tr_in = nullptr;  // modal face traces of `in` on tile boundaries (null: from the state)
   double* tr_out = nullptr;       // where to write those of `out` (may be null)
   // tab: out = u + dt (sum_j terms.a[j] terms.K[j] + ka_cur R(in)) instead of cu u + cw (in + dt R),
-  // R(in) stored in k_out (may be null), limiter flags OR-ed into flag_lim
+  // R(in) stored in k_out (may be null)
   int tab = 0;
   RkTerms terms{};
   double ka_cur = 0.0;
   double* k_out = nullptr;
+  int flag_or = 0;                     // limiter flags OR-ed into flag_lim (set only where it acts)
+  unsigned char* flag_zero = nullptr;  // flags that no stage sets, cleared by the wave kernel (may be null)
+  StageDt sdt{};
 };
 bool fused2d_supported(const KParams& P);
 bool fused2d_whole(const KParams& P);  // p = 3 elements in whole tiles: every precision's instances exist

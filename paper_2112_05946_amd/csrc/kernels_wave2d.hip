@@ -574,7 +574,7 @@ k_stage2w(KParams P, StageArgs A, const double* __restrict__ PhiT, const double*
     }
     return;
   }
-  const double dt = *P.dt;
+  const double dt = stage_dt(P, A.sdt);
   double o[M];
   if constexpr (!SSP) {
     // the earlier stages' terms first, in stage order, then this stage's
@@ -632,6 +632,7 @@ k_stage2w(KParams P, StageArgs A, const double* __restrict__ PhiT, const double*
   } else if (tid % 64 == 0 && inside && A.flag_lim && !A.flag_or) {
     A.flag_lim[e] = 0;
   }
+  if (!SSP && tid % 64 == 0 && inside && A.flag_zero) A.flag_zero[e] = 0;
 
   if (own) {
 #pragma unroll

@@ -34,6 +34,8 @@ struct StageArgs {
   double ka_cur;
   double* k_out;
   int flag_or;               // limiter flags OR-ed into flag_lim (set only where it acts)
+  unsigned char* flag_zero;  // flags cleared by this stage (may be null)
+  StageDt sdt;
 };
 
 inline StageArgs stage_args(const FusedStage& S) {
@@ -56,7 +58,9 @@ inline StageArgs stage_args(const FusedStage& S) {
   }
   A.ka_cur = S.ka_cur;
   A.k_out = S.k_out;
-  A.flag_or = S.tab;
+  A.flag_or = S.flag_or;
+  A.flag_zero = S.flag_zero;
+  A.sdt = S.sdt;
   return A;
 }
 
