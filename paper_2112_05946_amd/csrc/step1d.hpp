@@ -63,31 +63,38 @@ struct Op {
   static constexpr int lL = 0, lR = n, dhL = 2 * n, dhR = 3 * n, mean = 4 * n, D = 5 * n, Vinv = D + n * n,
                        V = Vinv + n * n;
 };
-// velocity-free primitives of the 1D Euler equations in FP64: one reciprocal of the density
-// serves velocity and pressure (the FP32-mixed loop keeps the divisions of the stage kernel)
-__device__ __forceinline__ void euler1_prim(const double* U, double g, double& ir, double& v, double& p) {
-  ir = recip(U[0]);
-  v = U[1] * ir;
-  p = (g - 1.0) * (U[2] - 0.5 * U[1] * v);
+// Quotients by one positive number: its reciprocal, and for each numerator the product corrected by
+// its remainder, which rounds like the division (three operations beside the shared reciprocal
+// instead of a dozen).  So the Euler equations in FP64 round as in the stage kernel: where the
+// limiter has set a pressure to its floor, the next stage's test on it is a tie that the last bit
+// decides.  (The FP32-mixed loop keeps the divisions of the stage kernel.)
+struct Quotient {
+  double r, d;
+  __device__ __forceinline__ explicit Quotient(double x) : r(recip(x)), d(x) {}
+  __device__ __forceinline__ double operator()(double a) const {
+    const double q = a * r;
+    return fma(fma(-d, q, a), r, q);
+  }
+};
+__device__ __forceinline__ double euler1_p(const double* U, const Quotient& by_rho, double g) {
+  const double kin = by_rho(0.5 * U[1] * U[1]);
+  return (g - 1.0) * (U[2] - kin);
+}
+__device__ __forceinline__ void euler1_f(const double* U, double v, double p, double* F) {
+  F[0] = U[1];
+  F[1] = U[1] * v + p;
+  F[2] = (U[2] + p) * v;
 }
 template <int EQ, typename R>
 __device__ __forceinline__ R pressure_of(const R* U, R g) {
-  if constexpr (EQ == kEuler1 && sizeof(R) == sizeof(double)) {
-    double ir, v, p;
-    euler1_prim(U, g, ir, v, p);
-    return p;
-  } else {
-    return pressure<EQ>(U, g);
-  }
+  if constexpr (EQ == kEuler1 && sizeof(R) == sizeof(double)) return euler1_p(U, Quotient(U[0]), g);
+  else return pressure<EQ>(U, g);
 }
 template <int EQ, typename R>
 __device__ __forceinline__ void flux_of(const R* U, R* F, R adv, R g) {
   if constexpr (EQ == kEuler1 && sizeof(R) == sizeof(double)) {
-    double ir, v, p;
-    euler1_prim(U, g, ir, v, p);
-    F[0] = U[1];
-    F[1] = U[1] * v + p;
-    F[2] = (U[2] + p) * v;
+    const Quotient by_rho(U[0]);
+    euler1_f(U, by_rho(U[1]), euler1_p(U, by_rho, g), F);
   } else {
     flux<EQ, 0>(U, F, adv, g);
   }
@@ -95,9 +102,9 @@ __device__ __forceinline__ void flux_of(const R* U, R* F, R adv, R g) {
 template <int EQ>
 __device__ __forceinline__ double speed_of(const double* U, double adv, double g) {
   if constexpr (EQ == kEuler1) {
-    double ir, v, p;
-    euler1_prim(U, g, ir, v, p);
-    return fabs(v) + sqrt(g * p * ir);
+    const Quotient by_rho(U[0]);
+    const double c = sqrt(by_rho(g * euler1_p(U, by_rho, g)));
+    return fabs(by_rho(U[1])) + c;
   } else {
     return speed<EQ, 0>(U, adv, g);
   }
@@ -107,22 +114,22 @@ __device__ __forceinline__ void interface_of(int kind, const R* L, const R* Rt, 
   if constexpr (EQ == kEuler1 && sizeof(R) == sizeof(double)) {
     double fL[3], fR[3], vL, vR, cL, cR;
     auto side = [&](const double* U, double* f, double& v, double& c) {
-      double ir, p;
-      euler1_prim(U, g, ir, v, p);
-      f[0] = U[1];
-      f[1] = U[1] * v + p;
-      f[2] = (U[2] + p) * v;
-      c = sqrt(g * p * ir);
+      const Quotient by_rho(U[0]);
+      v = by_rho(U[1]);
+      const double p = euler1_p(U, by_rho, g);
+      euler1_f(U, v, p, f);
+      c = sqrt(by_rho(g * p));
     };
     side(L, fL, vL, cL);
     side(Rt, fR, vR, cR);
     if (kind == FRSG_FLUX_HLL) {
-      const double SL = fmin(vL - cL, vR - cR), SR = fmax(vL + cL, vR + cR), iw = recip(SR - SL);
+      const double SL = fmin(vL - cL, vR - cR), SR = fmax(vL + cL, vR + cR);
+      const Quotient by_fan(SR - SL);
 #pragma unroll
       for (int s = 0; s < 3; ++s)
         Fs[s] = (SL >= 0.0) ? fL[s]
               : (SR <= 0.0) ? fR[s]
-                            : (SR * fL[s] - SL * fR[s] + (SL * SR) * (Rt[s] - L[s])) * iw;
+                            : by_fan(SR * fL[s] - SL * fR[s] + (SL * SR) * (Rt[s] - L[s]));
     } else {
       const double lam = fmax(fabs(vL) + cL, fabs(vR) + cR);
 #pragma unroll
@@ -386,7 +393,8 @@ __device__ __forceinline__ void run(const KParams& P, const Args& A, double* sme
   };
   // the elements that failed the test (every thread calls it, after a barrier): beta1 from the
   // nodes' density minima that the test left, pressure roots, beta2; then the coefficients in
-  // sA and the nodal values V.  Near a shock some workgroup comes here in most stages, and
+  // sA, from which the pass expands the nodal values anew (taking them along through the affine map
+  // saves 1.5 us per step of Sod, but rounds differently).  Near a shock some workgroup comes here in most stages, and
   // the launch lasts as long as that one
   auto limit_fix = [&](double (&V)[S][N]) {
     if constexpr (S > 1) {
@@ -434,15 +442,6 @@ __device__ __forceinline__ void run(const KParams& P, const Args& A, double* sme
             double v = C[s * M * n + it];
             if (s == 0) v = beta1 * (v - ub[0] * m0) + ub[0] * m0;
             C[s * M * n + it] = beta2 * (v - ub[s] * m0) + ub[s] * m0;
-          }
-        // the map is affine, so it takes the nodal values along
-#pragma unroll
-        for (int s = 0; s < S; ++s)
-#pragma unroll
-          for (int j = 0; j < n; ++j) {
-            double x = V[s][j];
-            if (s == 0) x = beta1 * (x - ub[0]) + ub[0];
-            V[s][j] = beta2 * (x - ub[s]) + ub[s];
           }
       }
     }
@@ -502,10 +501,10 @@ __device__ __forceinline__ void run(const KParams& P, const Args& A, double* sme
       const bool test = S > 1 && A.limit && st > 0 && !tested;
       if (in_slot && !(tested && !sBad[ls])) {
         if constexpr (F64) {
-          if (!tested) expand(X, U);
+          expand(X, U);
           if (test) limit_test(U);
         } else {
-          if (test || (done && !tested)) expand(X, Ud);
+          if (test || done) expand(X, Ud);
           if (test) limit_test(Ud);
           if (!done) expand(X, U);
         }
