@@ -244,7 +244,9 @@ fr_sg_status fr_sg_init(const fr_sg_problem* problem, void* hip_stream, void* wo
  * image, one per GPU, held from the library's first use on that GPU until the
  * process ends; the caller passes no workspace.  Problems whose
  * fr_sg_workspace_size exceeds 64 MiB are rejected with FRSG_EUNSUPPORTED and a
- * message naming both sizes.  Every context made by this call on one GPU shares
+ * message naming both sizes (an FP64 quadrilateral problem that exceeds it by
+ * less than the growth of its face-trace buffers over 4 x 2-element tiles is
+ * taken and runs without them: same results, its steps some per cent slower).  Every context made by this call on one GPU shares
  * that GPU's array: a later fr_sg_init_static on the same GPU overwrites the
  * tables and scalars of the earlier contexts (destroy them first), and calls on
  * such contexts that overlap in time race.  The array keeps the last call's

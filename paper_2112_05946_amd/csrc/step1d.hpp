@@ -27,12 +27,12 @@
 // the same step with one launch per stage: both give the same bits.
 //
 // Measured (FP64, per step, against one launch per stage): Burgers 1024 elements 24.1 -> 13.7 us,
-// Sod 2048 elements 50 -> 31.6, Sod with HLL and Bogacki-Shampine, 1501 elements, 58 -> 32.3, one
+// Sod 2048 elements 50 -> 32.3, Sod with HLL and Bogacki-Shampine, 1501 elements, 57 -> 33.4, one
 // RK4 step of the 64-element wave problem 32.8 -> 15.8; 64-element advection, every step in one
 // launch, 13.4 -> 6.9.  What is left is latency: a wave alone on its SIMD issues an FP64
 // instruction every 8 cycles or so, which is why a thread holds one node (two nodes per thread
 // halve the LDS reads but measured 14.5 on Burgers, and spill on Sod), and why a system's
-// workgroup takes 512 threads (34.0 with 384) although its node phases fill fewer.
+// workgroup takes 512 threads (a fourteenth faster than 384) although its node phases fill fewer.
 //
 // The step does not run in place (a workgroup reads its neighbours' elements at its
 // own time), except where one workgroup holds the whole mesh.
@@ -394,7 +394,8 @@ __device__ __forceinline__ void run(const KParams& P, const Args& A, double* sme
   // the elements that failed the test (every thread calls it, after a barrier): beta1 from the
   // nodes' density minima that the test left, pressure roots, beta2; then the coefficients in
   // sA, from which the pass expands the nodal values anew (taking them along through the affine map
-  // saves 1.5 us per step of Sod, but rounds differently).  Near a shock some workgroup comes here in most stages, and
+  // saves 1.5 us per step of Sod, but rounds differently).  Near a shock some workgroup comes here
+  // in most stages, and
   // the launch lasts as long as that one
   auto limit_fix = [&](double (&V)[S][N]) {
     if constexpr (S > 1) {
