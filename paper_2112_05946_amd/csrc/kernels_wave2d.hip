@@ -18,7 +18,7 @@
 // flux divergence is summed before the interface flux, and the weights' and the lane's place are
 // computed anew where they are used.
 //
-// Measured with 15 modes and 25 nodes, p = 3: 94 us per Butcher-row stage at 100 x 50 elements
+// Measured with 15 modes and 25 nodes, p = 3: 90 us per Butcher-row stage at 100 x 50 elements
 // (k_stage2d 136), 92 per SSP stage at 112 x 56 (99).  At 192 x 96 the vector units issue two
 // thirds of the time, at about 2.1 GHz, and the states pass at 2.3 of the 5.4 TB/s of a large copy;
 // the rest is waits at the ends of a workgroup.
