@@ -338,7 +338,12 @@ struct TriPostShared {
   double lam[M * Sh::NPT];  // filter factors of the step (exponential: exp(-alpha dt f))
   double num[Sh::EPB][Sh::NPT], den[Sh::EPB][Sh::NPT];
   double mn[Sh::EPB][2][Sh::TPE];
-  int need[Sh::EPB], any;
+  int need[Sh::EPB], any;  // elements whose bound fails, and whether there is one
+  // by the callers, before a barrier that comes ahead of post_tri: any of its waves sets them
+  __device__ __forceinline__ void clear() {
+    if ((int)threadIdx.x < Sh::EPB) need[threadIdx.x] = 0;
+    if (threadIdx.x == 0) any = 0;
+  }
 };
 
 // End-of-stage work on triangles with the stage kernel's lane layout: the sensor-gated
@@ -352,7 +357,7 @@ struct TriPostShared {
 // averaged with the triangle's quadrature weights.  c[] and sC are updated in place; a[]
 // receives the final modal traces at flux point `slot` (flux-point lanes), which the limiter
 // needs and the next launch reads.  Returns whether the lane's element changed.  Every thread
-// of the block calls it, with sC complete and visible.
+// of the block calls it, with sC complete and sh.need, sh.any cleared, both visible.
 //
 // The sums over an element's points are taken by every lane from LDS (one barrier), and the
 // detector's transform of the first variable is shared out over the four lanes of a point:
@@ -364,12 +369,10 @@ __device__ __forceinline__ bool post_tri(const KParams& P, double (&c)[M], doubl
                                          const double* sLf, TriPostShared<PD, M>& sh, const int e, const int le,
                                          const int rem, const bool active, const double dt, const TriPost& post) {
   using Sh = TriShape<PD>;
-  constexpr int NPT = Sh::NPT, NF = Sh::NF, TPE = Sh::TPE, EPB = Sh::EPB;
+  constexpr int NPT = Sh::NPT, NF = Sh::NF, TPE = Sh::TPE;
   const int slot = rem >> 2, s = rem & 3;
   const bool pt = active && slot < NPT;
   const bool fp = active && slot < NF;
-  if ((int)threadIdx.x < EPB) sh.need[threadIdx.x] = 0;
-  if (threadIdx.x == 0) sh.any = 0;
   bool filtered = false;
   if (post.filter) {
     for (int i = threadIdx.x; i < M * NPT; i += blockDim.x) {
@@ -661,6 +664,7 @@ __global__ void __launch_bounds__(TriShape<PD>::NT, 3)
   __shared__ TriPostShared<PD, M> sh;
   const int E = P.E, e0 = tri_block() * EPB;
   if (e0 >= E) return;
+  sh.clear();
   for (int i = threadIdx.x; i < NF * NPT; i += NT) sLf[i] = P.tri_Lf[i];
   {
     const int n = min(EPB, E - e0) * kTriGeo;
@@ -972,6 +976,7 @@ __global__ void __launch_bounds__(TriShape<PD>::NT) k_limit_tri(KParams P, const
   __shared__ TriPostShared<PD, M> sh;
   const int E = P.E, e0 = tri_block() * EPB;
   if (e0 >= E) return;
+  sh.clear();
   for (int i = threadIdx.x; i < Sh::NF * NPT; i += Sh::NT) sLf[i] = P.tri_Lf[i];
   const TriLane<PD> me((int)threadIdx.x, e0, E);
   const long EN = (long)E * NPT, mine_at = me.state_at(E, M);
