@@ -111,21 +111,31 @@ struct Plan {
   size_t lds = 0;
 };
 
+// a system's projection and staging have use for every wave; a scalar problem's for four
+int least_threads(const KParams& P) { return P.S > 1 ? kMaxThreads : 256; }
+
 // stages kept: right-hand sides a tableau step holds beside the two states
 Plan plan_of(const KParams& P, int nst, int nk) {
   Plan L;
   L.NqS = step1d::node_row(P.Nq);
   const int H = nst;
   // about one workgroup per compute unit: fewer elements only repeat more of the
-  // neighbours' work, more leave compute units idle
+  // neighbours' work, more leave compute units idle.  Beyond 16 elements only where a large
+  // mesh has so few nodes that 16 would leave the workgroup's threads idle, and with two
+  // workgroups per compute unit left, scalar four (Sod, 3 nodes, 49,152 elements, four steps:
+  // 470 us with a launch per stage, 814 with 16 elements, 262 with 79).  12 to 14 nodes fill a
+  // scalar problem's four waves with a few elements less (Burgers, 12 nodes, 16,384 elements:
+  // 199 us with a launch per stage, 203 with 16 elements, 151 with 15)
   int EB = std::min(16, std::max(4, (P.E + 255) / 256));
+  const int least = least_threads(P), wide = least / P.Nq - 2 * H;
+  if (wide > 16) EB = std::max(EB, std::min(wide, P.E / (P.S > 1 ? 512 : 1024)));
+  else if (P.S == 1 && wide >= 12 && P.E > 8192) EB = wide;
   for (; EB >= 4; --EB) {
     L.W = EB + 2 * H;
     const int need = (L.W * P.Nq + 63) / 64 * 64;
     L.lds = sizeof(double) * (size_t)step1d::lds_layout(P.S, P.M, P.np1, L.W, L.NqS, nk).total;
     if (need > kMaxThreads || L.lds > kMaxLds || L.W > 256) continue;
-    // (a system's projection and staging have use for every wave; a scalar problem's for four)
-    L.threads = std::max(P.S > 1 ? kMaxThreads : 256, need);
+    L.threads = std::max(least, need);
     L.EB = EB;
     L.grid = (P.E + EB - 1) / EB;
     return L;
@@ -171,6 +181,31 @@ hipError_t with_eq_n(const KParams& P, F&& f) {
   }
 }
 
+// Whether the step in one launch is the faster one.  With at most one workgroup per compute unit a
+// step is a chain of latencies, and it always is (on each of 676 problems of 2048 elements or more).
+// Beyond that the work counts: a workgroup computes EB + 2 (stages - 1), .. EB elements for EB, the stage
+// kernel EB' + 2 per launch for EB' = 256 / N_q - 2.  Over 3 to 64 nodes and up to 49,152
+// elements (figures: four steps, against a launch per stage) one launch loses
+//  - on p = 4 scalar problems of more than 256 threads, whose registers leave one workgroup per
+//    compute unit (Burgers, 40 nodes, RK4, 16,384 elements: 1379 us against 902); not with 16 or 32
+//    and more nodes and 8 elements, where the stage kernel's own rows collide in LDS or hold few
+//    elements (0.7 to 0.95 of its time), and not where its three passes over the state miss
+//    the L2 caches (24 nodes, 49,152 elements: 979 against 1233);
+//  - on FP32-mixed systems, which expand the state in both types, with few elements per workgroup
+//    or an almost empty second round (Sod, 24 nodes, 4096 elements: 317 against 292);
+//  - on four-stage steps of systems, whose stored right-hand sides leave room for few elements
+//    (p = 4 Sod, RK4, 16,384 elements, five per workgroup: 1988 against 1277).
+bool pays(const KParams& P, const Plan& L, int stages, bool tab) {
+  if (L.grid <= 256) return true;
+  const bool p4 = P.np1 == 5, few = L.EB >= 8 && (P.Nq % 16 == 0 || (p4 && P.Nq >= 32));
+  if (P.S == 1)
+    return !p4 || L.threads <= 256 || few || (P.eq == kAdvection && P.fp32) ||
+           (!tab && L.EB >= 6 && sizeof(double) * (double)P.M * P.E * P.np1 >= 16e6);
+  if (P.fp32) return few || (L.grid >= 512 && L.EB >= (P.np1 <= 3 ? 8 : 10));
+  if (stages < 4) return few || !p4 || L.grid >= 512;
+  return L.EB >= 10 || (L.EB >= 6 && P.Nq >= 32);
+}
+
 }  // namespace
 
 // Steps of up to four stages of FR degree 1..4 (FP32-mixed: SSP-RK3 only) whose window of at
@@ -179,7 +214,8 @@ hipError_t with_eq_n(const KParams& P, F&& f) {
 bool step1d_supported(const KParams& P, int stages, bool tab) {
   if (P.dim != 1 || P.bf16 || (P.fp32 && tab) || P.np1 < 2 || P.np1 > 5) return false;
   if (stages < 1 || stages > step1d::kMaxStages) return false;
-  return plan_of(P, stages, tab ? stages - 1 : 0).EB > 0 && cfl_eb(P) >= 1;
+  const Plan L = plan_of(P, stages, tab ? stages - 1 : 0);
+  return L.EB > 0 && cfl_eb(P) >= 1 && pays(P, L, stages, tab);
 }
 // per-workgroup maxima of a step or of a CFL pass, at most
 long step1d_partials(const KParams& P) { return std::max<long>((P.E + 3) / 4, cfl_eb(P) > 0 ? (P.E + cfl_eb(P) - 1) / cfl_eb(P) : 0) + 1; }
