@@ -331,6 +331,10 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   c->quad = !c->is_tri && quad_mfma_supported(K) &&
             (P.precision == FRSG_BF16_SPLIT ||
              (P.precision == FRSG_FP64 && P.integrator == FRSG_SSPRK3 && quad_fp64_modes(K.M) && one_round));
+  // (its trace buffers and the wave kernel's are of one size)
+  c->quad_rhs = c->quad || (!c->is_tri && quad_mfma_supported(K) && P.precision == FRSG_FP64 && c->fused &&
+                            wave2d_chosen(K) && quad_fp64_rhs_modes(K.M) && !quad_fp64_modes(K.M) &&
+                            pair2d_blocks(K) <= kWaveSmall);
   c->fused_tri = c->is_tri && tri_fused_supported(K);
   c->fused1d = c->dim == 1 && fr1d_supported(K);
   const Tableau* tab_rk = tableau_of(P.integrator);
@@ -731,7 +735,7 @@ static fr_sg_status rhs_into(fr_sg_ctx* ctx, const double* u, double* dudt) {
     return timed(ctx, "stage_rhs", 2 * state_bytes(ctx), [&] {
       return launch_stage_tri(ctx->kp, u, u, dudt, 0.0, 1.0, 1, ctx->ws.Tm[0], 0, nullptr, ctx->stream);
     });
-  if (ctx->quad) {
+  if (ctx->quad_rhs && ctx->ws.tr[0]) {
     fr_sg_status st = timed(ctx, "traces", 0.0, [&] { return launch_quad_traces(ctx->kp, u, ctx->ws.tr[0], ctx->stream); });
     if (st != FRSG_OK) return st;
     QuadStage S{u, u, dudt, 0.0, 1.0, 0, nullptr, nullptr, nullptr, ctx->dDt, ctx->dcmax, ctx->dfrag,

@@ -254,6 +254,7 @@ struct fr_sg_ctx {
   const float* dPWT32 = nullptr;
   bool fused = false;            // fused 2D Euler stage kernel (FP32-mixed, and the element-wise passes)
   bool quad = false;             // matrix-core 2D Euler stage kernel (FP64, BF16-split)
+  bool quad_rhs = false;         // ... for fr_sg_rhs too (or for it alone)
   const double* dfrag = nullptr; // its operand tables
   bool fused1d = false;          // fused 1D stage kernel
   bool step1d = false;           // a whole 1D step in one launch
@@ -345,7 +346,9 @@ struct QuadStage {
   const double* tr_in;  // modal face traces of `in` on tile boundaries (required)
   double* tr_out;       // where to write those of `out` (may be null)
 };
-constexpr bool quad_fp64_modes(int M) { return M > 10; }  // modes with which FP64 steps may take it
+// modes with which the FP64 steps, and the right-hand side on its own, may take it
+constexpr bool quad_fp64_modes(int M) { return M > 10; }
+constexpr bool quad_fp64_rhs_modes(int M) { return M >= 10; }
 bool quad_mfma_supported(const KParams& P);
 // doubles of one modal face-trace buffer of the matrix-core path
 size_t quad_trace_count(int nx, int ny, int M);
@@ -356,24 +359,36 @@ hipError_t launch_quad_traces(const KParams& P, const double* u, double* tr, hip
 size_t fused2d_trace_count(const KParams& P, bool fp64);
 hipError_t launch_fused_stage(const KParams& P, const FusedStage& S, hipStream_t s);
 // ... in FP64 with one element per wave (kernels_wave2d.hip), nodes in groups of four, or with two
-// variables per lane and nodes in pairs (the pair kernel, k_stage2d).  The pair kernel keeps
-// the node counts that a group of four pads by more than an eighth (6 modes, 9 nodes, 100 x 50
-// elements: 0.52 against 0.58 ms per five steps).  It has two workgroups of 8 elements per compute
-// unit: with half of that or less (256 workgroups) a SIMD has one wave of it, and the wave kernel
-// wins (64 x 32 elements: 15 modes 0.59 against 0.70 ms, 10 modes 0.35 against 0.40).  From there to
-// a full round of workgroups (512) the pair kernel's round ends sooner (80 x 40: 0.81 against
-// 0.89 ms).  Beyond it the wave kernel's smaller workgroups leave less of the last round empty
-// and overlap one another's loads and node loops, at the price of a tenth more instructions per
-// element: with 15 modes that pays while the rounds are few (1.38 against 1.49 ms at 112 x 56, 2.04
-// against 2.18 at 144 x 72, 3.26 against 3.30 at 192 x 96; 10.93 against 10.92 per ten steps at
-// 256 x 128), with 10 it does not (1.62 against 1.52 at 160 x 80).
-constexpr bool wave2d_nodes(int nq) { return 8 * (((nq + 3) & ~3) - nq) <= nq; }
+// variables per lane and nodes in pairs (the pair kernel, k_stage2d).  The pair kernel has two
+// workgroups of 8 elements per compute unit: with half of that or less (256 workgroups) a SIMD has
+// one wave of it, and the wave kernel wins (64 x 32 elements: 15 modes 0.59 against 0.70 ms, 10
+// modes 0.35 against 0.40).  From there to a full round of workgroups (512) the pair kernel's round
+// ends sooner (80 x 40: 0.81 against 0.89 ms).  Beyond it the wave kernel's smaller workgroups leave
+// less of the last round empty and overlap one another's loads and node loops, at the price of
+// a tenth more instructions per element: with 15 modes that pays while the rounds are few (1.38
+// against 1.49 ms at 112 x 56, 2.04 against 2.18 at 144 x 72, 3.26 against 3.30 at 192 x 96; 10.93
+// against 10.92 per ten steps at 256 x 128), with 10 it does not (1.62 against 1.52 at 160 x 80).
+// A group of four pads 9 nodes by a third: they go to the wave kernel only where its one wave per
+// element fills no SIMD twice (four steps, 154 against 216 us at 18 x 10, 169 against 220 at 30 x 34;
+// 0.58 against 0.52 ms per five at 100 x 50), and 5 nodes (padded to 8) never.
+constexpr int wave2d_padding(int nq) { return ((nq + 3) & ~3) - nq; }
+constexpr bool wave2d_nodes(int nq) { return 3 * wave2d_padding(nq) <= nq; }
 constexpr int kWaveTile = 2;  // workgroup of the wave kernel: 2 x 2 elements
 inline int wave2d_tiles(int nx, int ny) { return ((nx + kWaveTile - 1) / kWaveTile) * ((ny + kWaveTile - 1) / kWaveTile); }
+inline long pair2d_blocks(const KParams& P) { return (long)((P.nx + 3) / 4) * ((P.ny + 1) / 2); }
+constexpr long kWaveSmall = 144;  // workgroups of the pair kernel
 inline bool wave2d_chosen(const KParams& P) {
-  const long pair_blocks = (long)((P.nx + 3) / 4) * ((P.ny + 1) / 2);
-  return wave2d_nodes(P.Nq) && (pair_blocks <= 256 || (pair_blocks > 512 && pair_blocks <= 2560 && P.M > 10));
+  const long blocks = pair2d_blocks(P);
+  if (!wave2d_nodes(P.Nq)) return false;
+  if (8 * wave2d_padding(P.Nq) > P.Nq) return blocks <= kWaveSmall;
+  return blocks <= 256 || (blocks > 512 && blocks <= 2560 && P.M > 10);
 }
+// A right-hand side on its own has no traces of its input and takes them from the neighbours'
+// states, twice as many per element with the wave kernel's tiles: with up to 10 modes the pair
+// kernel is ahead from fewer workgroups on (64 x 32 elements: 10 modes 27.9 against 29.2 us, 3
+// modes 11.0 against 11.8; 32 x 16 9.7 against 9.0).  Small even p = 3 meshes of 10 modes take the
+// matrix-core kernel with a trace pass before it (18 x 10: 15.1 us against the wave kernel's 18.4).
+inline bool wave2d_rhs(const KParams& P) { return wave2d_chosen(P) && (P.M > 10 || pair2d_blocks(P) <= kWaveSmall); }
 hipError_t launch_wave_stage(const KParams& P, const FusedStage& S, hipStream_t s);
 hipError_t launch_fused_cfl(const KParams& P, const double* u, unsigned long long* lam, hipStream_t s);
 // sensor-gated filter and/or limiter in place, with the fused kernel's tile layout

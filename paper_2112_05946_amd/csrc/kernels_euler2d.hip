@@ -1103,7 +1103,7 @@ bool fused2d_supported(const KParams& P) {
 }
 
 hipError_t launch_fused_stage(const KParams& P, const FusedStage& S, hipStream_t s) {
-  if (!S.fp32 && wave2d_chosen(P)) return launch_wave_stage(P, S, s);
+  if (!S.fp32 && (S.stage == 0 ? wave2d_rhs(P) : wave2d_chosen(P))) return launch_wave_stage(P, S, s);
 #define X(MM, QQ) if (P.M == MM && P.Nq == QQ) return launch_stage_t<MM, QQ>(P, S, s);
   FRSG_FUSED_SIZES(X)
 #undef X

@@ -930,7 +930,7 @@ static hipError_t launch_quad_t(const KParams& P, const QuadStage& S, hipStream_
       hipLaunchKernelGGL((k_quad_stage<M, NQ, kQBF16, FRSG_FLUX_HLL>), dim3(ntiles), dim3(QBLK), 0, s, P, A);
     else
       hipLaunchKernelGGL((k_quad_stage<M, NQ, kQBF16, FRSG_FLUX_RUSANOV>), dim3(ntiles), dim3(QBLK), 0, s, P, A);
-  } else if constexpr (quad_fp64_modes(M)) {
+  } else if constexpr (quad_fp64_rhs_modes(M)) {
     if (hll)
       hipLaunchKernelGGL((k_quad_stage<M, NQ, kQF64, FRSG_FLUX_HLL>), dim3(ntiles), dim3(QBLK), 0, s, P, A);
     else
