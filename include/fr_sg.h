@@ -244,9 +244,14 @@ fr_sg_status fr_sg_init(const fr_sg_problem* problem, void* hip_stream, void* wo
  * image, one per GPU, held from the library's first use on that GPU until the
  * process ends; the caller passes no workspace.  Problems whose
  * fr_sg_workspace_size exceeds 64 MiB are rejected with FRSG_EUNSUPPORTED and a
- * message naming both sizes (an FP64 quadrilateral problem that exceeds it by
- * less than the growth of its face-trace buffers over 4 x 2-element tiles is
- * taken and runs without them: same results, its steps some per cent slower).  Every context made by this call on one GPU shares
+ * message naming both sizes, except where they exceed it by what steps only run
+ * faster with, or by a table that has 8 KiB of its own beside the array.  Such a
+ * problem is taken: in 1D (the tables and CFL maxima of the one-launch step) its
+ * steps take a launch per stage, bit for bit the same results; on FP64
+ * quadrilaterals (the face traces, beyond those over 4 x 2-element tiles) they
+ * interpolate the neighbours' traces, same results, some per cent slower;
+ * triangles run as they are.
+ * Every context made by this call on one GPU shares
  * that GPU's array: a later fr_sg_init_static on the same GPU overwrites the
  * tables and scalars of the earlier contexts (destroy them first), and calls on
  * such contexts that overlap in time race.  The array keeps the last call's

@@ -276,7 +276,7 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   c->tab_off.clear();
   if (c->dim == 2 && !c->is_tri) build_quad_fragments(c->T);
   for (const std::vector<double>* v : {&T.r, &T.w, &T.D, &T.lL, &T.lR, &T.dhL, &T.dhR, &T.V, &T.Vinv, &T.Phi, &T.PW,
-                                       &T.filt, &T.shell, &T.swts, &T.Dt, &T.cmax, &T.PhiT, &T.PWT, &T.qfrag, &T.PWB, &T.op1}) {
+                                       &T.filt, &T.shell, &T.swts, &T.Dt, &T.cmax, &T.PhiT, &T.PWT, &T.qfrag}) {
     c->tab_off.push_back(blob.size());
     blob.insert(blob.end(), v->begin(), v->end());
   }
@@ -355,8 +355,16 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   c->host_tri.clear();
   if (c->is_tri) {
     const TriTables& R = c->tri;
-    for (const std::vector<double>* v : {&R.Dr, &R.Ds, &R.Lf, &R.lift, &R.geo, &R.V, &R.Vinv, &R.rows})
+    for (const std::vector<double>* v : {&R.Dr, &R.Ds, &R.Lf, &R.lift, &R.geo, &R.V, &R.Vinv})
       c->host_tri.insert(c->host_tri.end(), v->begin(), v->end());
+  }
+  // tables of the whole-step 1D kernel, of the fused triangle stage
+  c->host_more.clear();
+  if (c->step1d) {
+    c->host_more = T.PWB;
+    c->host_more.insert(c->host_more.end(), T.op1.begin(), T.op1.end());
+  } else if (c->fused_tri) {
+    c->host_more = c->tri.rows;
   }
   // FP32 copies of the node-major chaos tables (fused 2D path)
   c->host_f32.clear();
@@ -386,7 +394,7 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   const bool adj = c->dim == 1 && c->S == 1;
   const size_t nadj_part = adj ? (size_t)std::max(adjoint_partials(K), adj1d_partials(K)) : 0;
   const size_t ntr = c->quad ? quad_trace_count(P.nx, P.ny, T.M) : c->fused ? fused2d_trace_count(K, P.precision == FRSG_FP64) : 0;
-  const size_t nlam = c->dim == 1 ? (size_t)step1d_partials(K) : 0;
+  const size_t nlam = c->step1d ? (size_t)step1d_partials(K) : 0;
   L.sc = take(256);
   L.tab = take(blob.size() * sizeof(double));
   L.f32 = take(c->host_f32.size() * sizeof(float));
@@ -407,23 +415,31 @@ static fr_sg_status prepare(const fr_sg_problem& problem, fr_sg_ctx* c, std::str
   L.nrk = nrk;
   L.tm0 = take(ntm * 8);
   L.tm1 = take(ntm * 8);
-  L.lam0 = take(nlam * 8);
-  L.lam1 = take(nlam * 8);
   L.adj = adj;
   L.has_tr = ntr > 0;
   L.has_tm = ntm > 0;
-  // the traces last: the static workspace takes a problem whose buffers for the larger of the two
-  // tiles fit, and runs it without them where they do not fit for its own
-  L.least = o + (c->fused && !c->quad ? 2 * align_up(fused2d_trace_count(K, false) * 8) : 0);
+  // Last what the static workspace can do without (1D: the whole-step kernel, so that steps take a
+  // launch per stage; 2D: the face traces), or has room for beside its 64 MiB (triangles: the
+  // operators by row groups).  It takes a problem by the rest alone, and by face traces over the
+  // smaller of the two tiles
+  L.opt = L.least = o;
+  L.more = take(c->host_more.size() * sizeof(double));
+  L.lam0 = take(nlam * 8);
+  L.lam1 = take(nlam * 8);
   L.tr0 = take(ntr * 8);
   L.tr1 = take(ntr * 8);
   L.total = o;
-  if (!c->fused || c->quad) L.least = L.total;
-  L.least = std::min(L.least, L.total);
+  L.need = c->fused_tri || c->quad ? L.total : L.opt;
+  if (c->quad) L.least = L.total;
+  else if (c->fused) {
+    size_t faces = fused2d_trace_count(K, false);
+    if (quad_mfma_supported(K)) faces = std::min(faces, quad_trace_count(P.nx, P.ny, T.M));
+    L.least = std::min(L.total, L.opt + 2 * align_up(faces * 8));
+  }
   return FRSG_OK;
 }
 
-// workspace of a problem, and the least that init_with_workspace takes without check_device
+// workspace of a problem, and what of it counts against the static workspace's size
 fr_sg_status frsg::workspace_sizes(const fr_sg_problem* problem, int64_t* bytes, int64_t* least) {
   if (!problem || !bytes) {
     g_init_error = "problem and bytes must not be NULL";
@@ -487,7 +503,7 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
     return st;
   }
   const Layout& L = c->lay;
-  if (!workspace || workspace_bytes < (int64_t)(check_device ? L.total : L.least) || ((uintptr_t)workspace & 255u) != 0) {
+  if (!workspace || workspace_bytes < (int64_t)(check_device ? L.total : L.need) || ((uintptr_t)workspace & 255u) != 0) {
     g_init_error = "workspace must be a 256-byte aligned device buffer of at least " + std::to_string(L.total) +
                    " bytes (fr_sg_workspace_size)";
     delete c;
@@ -505,6 +521,7 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
   }
   c->stream = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
+  const bool whole = workspace_bytes >= (int64_t)L.total;
   // upload the tables into the workspace and clear the device scalars; the host
   // copies stay alive until the stream has finished with them
   hipError_t he = hipMemsetAsync(ws + L.sc, 0, 256, c->stream);
@@ -516,6 +533,9 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
                         c->stream);
   if (he == hipSuccess && !c->host_tri.empty())
     he = hipMemcpyAsync(ws + L.tri, c->host_tri.data(), c->host_tri.size() * sizeof(double), hipMemcpyHostToDevice,
+                        c->stream);
+  if (he == hipSuccess && whole && !c->host_more.empty())
+    he = hipMemcpyAsync(ws + L.more, c->host_more.data(), c->host_more.size() * sizeof(double), hipMemcpyHostToDevice,
                         c->stream);
   if (he == hipSuccess && c->is_tri)
     he = hipMemcpyAsync(ws + L.nbr, c->tri.nbr.data(), c->tri.nbr.size() * sizeof(int), hipMemcpyHostToDevice,
@@ -532,6 +552,8 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
   c->host_f32.shrink_to_fit();
   c->host_tri.clear();
   c->host_tri.shrink_to_fit();
+  c->host_more.clear();
+  c->host_more.shrink_to_fit();
 
   // device views of the tables
   const double* b = (const double*)(ws + L.tab);
@@ -559,8 +581,9 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
   tab.PhiT = c->dPhiT;
   tab.PWT = c->dPWT;
   c->dfrag = b + off[18];
-  tab.PWB = b + off[19];
-  tab.op1 = b + off[20];
+  c->step1d = c->step1d && whole;
+  tab.PWB = (const double*)(ws + L.more);
+  tab.op1 = tab.PWB + c->T.PWB.size();
   if (c->fused) {
     c->dPhiT32 = (const float*)(ws + L.f32);
     c->dPWT32 = c->dPhiT32 + c->T.PhiT.size();
@@ -577,7 +600,7 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
     K.tri_geo = K.tri_lift + R.lift.size();
     K.tri_V = K.tri_geo + R.geo.size();
     K.tri_Vinv = K.tri_V + R.V.size();
-    K.tri_rows = K.tri_Vinv + R.Vinv.size();
+    K.tri_rows = (const double*)(ws + L.more);
     K.tri_nbr = (const int*)(ws + L.nbr);
   }
   Workspace& W = c->ws;
@@ -600,7 +623,7 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
     W.Tm[0] = (double*)(ws + L.tm0);
     W.Tm[1] = (double*)(ws + L.tm1);
   }
-  if (L.has_tr && workspace_bytes >= (int64_t)L.total) {
+  if (L.has_tr && whole) {
     W.tr[0] = (double*)(ws + L.tr0);
     W.tr[1] = (double*)(ws + L.tr1);
   }

@@ -208,12 +208,14 @@ struct Layout {
   size_t w1 = 0, w2 = 0, un = 0, fn = 0, gn = 0, co = 0;
   size_t avb = 0, ab2 = 0, ab1 = 0, agt = 0, apt = 0;
   size_t tr0 = 0, tr1 = 0, tm0 = 0, tm1 = 0;
-  size_t lam0 = 0, lam1 = 0;
+  size_t more = 0, lam0 = 0, lam1 = 0;
   size_t rk[kRkMaxTerms] = {0};
   int nrk = 0;
   bool adj = false, has_tr = false, has_tm = false;
   size_t total = 0;
-  size_t least = 0;  // enough to run: without the face-trace buffers at the end where total exceeds it
+  size_t opt = 0;    // from here on what steps are faster with (and a triangle operator table)
+  size_t need = 0;   // enough to run
+  size_t least = 0;  // what counts against the size of the static workspace
 };
 
 }  // namespace frsg
@@ -269,6 +271,7 @@ struct fr_sg_ctx {
   std::vector<double> host_tab;      // tables waiting for the upload in fr_sg_init
   std::vector<size_t> tab_off;       // offsets of the tables in host_tab (and on the device)
   std::vector<double> host_tri;      // triangle operators and geometry
+  std::vector<double> host_more;     // tables of the whole-step 1D kernel or of the fused triangle stage
   std::vector<float> host_f32;       // FP32 chaos tables of the fused 2D path
   std::string err;
 };

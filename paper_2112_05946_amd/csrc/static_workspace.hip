@@ -10,12 +10,14 @@
 namespace {
 
 constexpr int64_t kStaticWorkspaceBytes = int64_t(64) << 20;  // 64 MiB per GPU
+// ... and beside them the fused triangle stage's operators by row groups (at most 7680 bytes)
+constexpr int64_t kStaticTableBytes = int64_t(8) << 10;
 constexpr int kMaxDevices = 64;
 
 // the array itself; host code never passes this name to a kernel or a copy (on the
 // host it only stands for the symbol): the device address comes from
 // hipGetSymbolAddress, once per device
-static __device__ __align__(256) unsigned char scratch[kStaticWorkspaceBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticWorkspaceBytes + kStaticTableBytes];
 
 std::mutex g_mu;
 void* g_scratch_ptr[kMaxDevices] = {nullptr};
@@ -58,5 +60,5 @@ extern "C" fr_sg_status fr_sg_init_static(const fr_sg_problem* problem, void* hi
     }
     ptr = g_scratch_ptr[dev];
   }
-  return frsg::init_with_workspace(problem, hip_stream, ptr, kStaticWorkspaceBytes, out, false);
+  return frsg::init_with_workspace(problem, hip_stream, ptr, kStaticWorkspaceBytes + kStaticTableBytes, out, false);
 }
