@@ -250,7 +250,7 @@ fr_sg_status fr_sg_init(const fr_sg_problem* problem, void* hip_stream, void* wo
  * steps take a launch per stage, bit for bit the same results; on FP64
  * quadrilaterals (the face traces, beyond those over 4 x 2-element tiles) they
  * interpolate the neighbours' traces, same results, some per cent slower;
- * triangles run as they are.
+ * triangles run as they are.  fr_sg_query reports the bytes in use.
  * Every context made by this call on one GPU shares
  * that GPU's array: a later fr_sg_init_static on the same GPU overwrites the
  * tables and scalars of the earlier contexts (destroy them first), and calls on

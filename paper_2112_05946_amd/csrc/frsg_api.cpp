@@ -629,7 +629,7 @@ fr_sg_status frsg::init_with_workspace(const fr_sg_problem* problem, void* hip_s
   }
   W.lam1d[0] = (double*)(ws + L.lam0);
   W.lam1d[1] = (double*)(ws + L.lam1);
-  W.bytes = L.total;
+  W.bytes = whole ? L.total : L.opt;
   K.dt = W.scal;
   K.lam_bits = (unsigned long long*)(W.scal + 1);
   K.status = (unsigned*)(W.scal + 2);  // scal[3] is the second CFL accumulator

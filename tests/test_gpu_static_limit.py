@@ -1,6 +1,7 @@
 """Problems at the limit of the static workspace run there with what fits: 1D steps with a launch per
 stage instead of whole (bit for bit the same states, time steps and switch decisions, the limiter
-acting), triangles and 2D meshes as they are."""
+acting), triangles and 2D meshes as they are; and the workspace that a context reports is the one it
+uses."""
 
 import numpy as np
 import pytest
@@ -51,8 +52,9 @@ def test_whole_steps_equal_a_launch_per_stage(label, cfg, start):
     else:
         u0 = inputs.fuzz_scalar(R.M, prob.E, prob.nsp, 3, scale=0.1, offset=0.8)
     u, du, fu, pu, _ = _run(cfg, u0, False, 3, dt)
-    v, dv, fv, pv, _ = _run(cfg, u0, True, 3, dt)
+    v, dv, fv, pv, used = _run(cfg, u0, True, 3, dt)
     assert pu <= {"cfl", "copy", "stage1"} and len(pv - {"cfl"}) > 1, (pu, pv)
+    assert used <= STATIC
     assert np.array_equal(du, dv) and np.array_equal(fu, fv) and np.array_equal(u, v)
     if prob.S > 1 and start == "near_vacuum":
         assert fu.reshape(3, 4, -1)[:, 0].any()
@@ -64,8 +66,8 @@ def test_2d_workspace_in_use():
     prob, (T, R) = oracle_for(cfg)
     u0 = project_initial(prob, cfg["ic"], (T, R))
     u, _, _, _, need = _run(cfg, u0, False, 2)
-    v, _, _, _, _ = _run(cfg, u0, True, 2)
-    assert need > STATIC
+    v, _, _, _, used = _run(cfg, u0, True, 2)
+    assert used <= STATIC < need
     assert rel_l2(v, u) < RTOL_FP64
 
 
@@ -77,6 +79,6 @@ def test_triangles_at_the_limit():
     cfg = dict(inputs.tri_shock_vortex(4), p=3, gpc_order=2, nq1d=3, mesh=mesh, bc=["outflow"] * 4)
     u0 = inputs.fuzz_euler(2, 6, n, 10, 3)
     u, du, fu, _, need = _run(cfg, u0, False, 2)
-    v, dv, fv, _, _ = _run(cfg, u0, True, 2)
-    assert STATIC < need <= STATIC + (8 << 10)
+    v, dv, fv, _, used = _run(cfg, u0, True, 2)
+    assert used == need and STATIC < used <= STATIC + (8 << 10)
     assert np.array_equal(u, v) and np.array_equal(du, dv) and np.array_equal(fu, fv)
