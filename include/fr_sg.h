@@ -316,10 +316,12 @@ fr_sg_status fr_sg_step(fr_sg_ctx* ctx, double* u, double dt, double* dt_used, u
  * can differ from that of a separate fr_sg_step call in the last bits; given
  * equal time steps the states are equal bit for bit.  A scalar 1D problem in
  * FP64 of FR degree <= 3 whose elements fit one workgroup ((E + 2) N_q <=
- * 1024, its stage data within 64 KB of LDS) runs the SSP-RK3 steps of the
- * call in one launch of one workgroup, with the same per-element arithmetic.
- * Other 1D steps take one launch each (FR degree <= 4, FP64 or FP32-mixed), in
- * which the state moves between u and the workspace; it ends in u.
+ * 1024, a stage's coefficients, traces and residuals within 64 KB) runs the
+ * SSP-RK3 steps of the call in one launch of one workgroup, with the same
+ * per-element arithmetic.  Other 1D steps of FR degree <= 4 (FP64 but for the
+ * six-stage tableau, FP32-mixed SSP-RK3) take one launch each beside the call's
+ * CFL or copy pass, where that is faster than a launch per stage; the state
+ * then moves between u and the workspace, and ends in u.
  * dt_used: device double[nsteps] or NULL; flags: device uint8[nsteps * 4 * E]
  * or NULL, laid out per step as in fr_sg_step. */
 fr_sg_status fr_sg_steps(fr_sg_ctx* ctx, double* u, int32_t nsteps, double* dt_used, uint8_t* flags);

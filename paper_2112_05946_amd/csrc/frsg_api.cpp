@@ -978,7 +978,8 @@ static fr_sg_status steps_resident1d(fr_sg_ctx* ctx, double* u, int nsteps, doub
   fr_sg_status st;
   Lam1d lam;
   if ((st = timed(ctx, "cfl", sb, [&] { return launch_cfl1d_part(K, u, W.lam1d[0], nullptr, &lam, s); }))) return st;
-  const char* name = fr1d_resident_lds_state(K) ? "steps_resident_lds" : "steps_resident";
+  // (one kernel, its states in LDS; the record's two names go by the size of the problem)
+  const char* name = fr1d_resident_small(K) ? "steps_resident_lds" : "steps_resident";
   // at most kChunk steps per launch (a few tens of milliseconds), the CFL maximum
   // handed from launch to launch
   constexpr int kChunk = 4096;

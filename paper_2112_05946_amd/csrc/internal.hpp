@@ -364,13 +364,17 @@ hipError_t launch_fused_stage(const KParams& P, const FusedStage& S, hipStream_t
 // ... in FP64 with one element per wave (kernels_wave2d.hip), nodes in groups of four, or with two
 // variables per lane and nodes in pairs (the pair kernel, k_stage2d).  The pair kernel has two
 // workgroups of 8 elements per compute unit: with half of that or less (256 workgroups) a SIMD has
-// one wave of it, and the wave kernel wins (64 x 32 elements: 15 modes 0.59 against 0.70 ms, 10
-// modes 0.35 against 0.40).  From there to a full round of workgroups (512) the pair kernel's round
-// ends sooner (80 x 40: 0.81 against 0.89 ms).  Beyond it the wave kernel's smaller workgroups leave
-// less of the last round empty and overlap one another's loads and node loops, at the price of
-// a tenth more instructions per element: with 15 modes that pays while the rounds are few (1.38
-// against 1.49 ms at 112 x 56, 2.04 against 2.18 at 144 x 72, 3.26 against 3.30 at 192 x 96; 10.93
-// against 10.92 per ten steps at 256 x 128), with 10 it does not (1.62 against 1.52 at 160 x 80).
+// one wave of it, and the wave kernel wins at every mode count and integrator (0.6 to 0.87 of its
+// time up to 64 x 32 elements).  From there to a full round of workgroups (512) the pair kernel's
+// round ends sooner; beyond it the wave kernel's smaller workgroups leave less of the last round
+// empty and overlap one another's loads and node loops, at the price of a tenth more instructions
+// per element, which pays with 15 modes while the rounds are few.  Four SSP-RK3 steps, p = 3, wave
+// against pair kernel in us: 15 modes 722 / 661 at 80 x 40, 937 / 1032 at 100 x 50, 2014 / 2140 at
+// 160 x 80, 2744 / 2737 at 192 x 96, 3622 / 3722 at 224 x 112, 4732 / 4638 at 256 x 128; 10 modes 420 /
+// 413, 567 / 638, 1314 / 1257 and 3127 / 2766 at the first three and the last of these; 3 modes 310 /
+// 273 at 100 x 50.  The line is the SSP-RK3 steps': Butcher rows of 15 modes at p = 3, in which
+// the pair kernel spills, would gain on the meshes it keeps too (746 / 977 at 80 x 40, 5425 /
+// 7286 at 256 x 128), at p = 2 they lose from 192 x 96 on (3593 / 3446).
 // A group of four pads 9 nodes by a third: they go to the wave kernel only where its one wave per
 // element fills no SIMD twice (four steps, 154 against 216 us at 18 x 10, 169 against 220 at 30 x 34;
 // 0.58 against 0.52 ms per five at 100 x 50), and 5 nodes (padded to 8) never.
@@ -511,7 +515,7 @@ hipError_t launch_copy_state(const double* a, double* b, long n, hipStream_t s);
 // workgroup, in one launch; lam_in holds the CFL maxima of u, lam_out receives
 // that of the result.  flags [nsteps][4][E] and dt_used [nsteps] may be null.
 bool fr1d_resident_fits(const KParams& P);
-bool fr1d_resident_lds_state(const KParams& P);  // the state takes little enough of the compute unit's LDS
+bool fr1d_resident_small(const KParams& P);  // the smaller of them, which the pass record names apart
 hipError_t launch_steps1d_resident(const KParams& P, double* u, int nsteps, int limit, unsigned char* flags,
                                    double* dt_used, const Lam1d& lam_in, double* lam_out, hipStream_t s);
 

@@ -280,12 +280,16 @@ hipError_t launch_step1d(const KParams& P, const Step1D& T, Lam1d* lam_out, hipS
 }
 
 // the one-workgroup multi-step kernel: FP64 scalar equations of FR degree <= 3, every element
-// in one workgroup's 1024 (element, node) pairs (at 1024 threads a lane has 128 registers: the
-// Euler and higher-degree instances would spill)
+// and two more in 1024 (element, node) pairs (at 1024 threads a lane has 128 registers: the Euler
+// and higher-degree instances would spill), and a stage's coefficients, traces and residuals (once
+// each, unpadded) and the chaos tables within 64 KB.  That is a cap on the work of one compute
+// unit, not on its LDS: the launch lays out at most 127 KB under it.  It lies about where a step of
+// one workgroup takes as long as a window step (Burgers, 9 modes, 16 nodes: 12.1 us at 40
+// elements, 14.4 at 56, against 13.8 at 57; p = 1, 3 nodes: 9.8 at 339, against 10.9 at 340).
 constexpr int kMaxNRes = 4;
-constexpr size_t kLdsRes = 64 * 1024;
+constexpr size_t kWorkRes = 64 * 1024;
 static size_t resident_state_bytes(const KParams& P) { return sizeof(double) * (size_t)P.S * P.M * P.np1 * P.E; }
-static size_t resident_lds(const KParams& P) {
+static size_t resident_work(const KParams& P) {
   const size_t nc = (size_t)P.S * P.M * P.np1, E = (size_t)P.E;
   return sizeof(double) * ((E + 2) * nc + (E + 2) * P.Nq * 2 * P.S + E * P.S * P.np1 * P.Nq + 2 * (size_t)P.M * P.Nq +
                            16 + 256);
@@ -293,10 +297,10 @@ static size_t resident_lds(const KParams& P) {
 bool fr1d_resident_fits(const KParams& P) {
   if (P.dim != 1 || P.fp32 || P.bf16 || P.eq == kEuler1 || P.np1 < 2 || P.np1 > kMaxNRes) return false;
   if ((long)(P.E + 2) * P.Nq > kMaxThreadsRes) return false;
-  return resident_lds(P) <= kLdsRes;
+  return resident_work(P) <= kWorkRes;
 }
-bool fr1d_resident_lds_state(const KParams& P) {
-  return fr1d_resident_fits(P) && resident_lds(P) + 3 * resident_state_bytes(P) <= kLdsRes;
+bool fr1d_resident_small(const KParams& P) {
+  return fr1d_resident_fits(P) && resident_work(P) + 3 * resident_state_bytes(P) <= kWorkRes;
 }
 
 template <int EQ, int N, int THREADS>

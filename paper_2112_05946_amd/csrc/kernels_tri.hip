@@ -1,9 +1,11 @@
 // Triangle path of the 2D Euler right-hand side (Sec. 3.5 multi-dimensional FR
-// on the triangles of Sec. 3.1), multi-pass like the generic quadrilateral path:
-// the nodal values and fluxes at (node, element, solution point) come from the
-// shared nodal pass; this file adds the interactive fluxes at the flux points,
-// the nodal residual (flux divergence plus the correction-field lifting) and
-// the CFL maximum.  Nodal arrays: [S][Nq][E][N_p]; face jumps: [S][Nq][E][3 nfp].
+// on the triangles of Sec. 3.1).  First the multi-pass kernels, for the mode and
+// node counts that the fused stage below is not compiled for: as on the generic
+// quadrilateral path the nodal values and fluxes at (node, element, solution
+// point) come from the shared nodal pass; these add the interactive fluxes at
+// the flux points, the nodal residual (flux divergence plus the correction-field
+// lifting) and the CFL maximum.  Nodal arrays: [S][Nq][E][N_p]; face jumps:
+// [S][Nq][E][3 nfp].  Then the fused stage, one launch per Runge-Kutta stage.
 #include "device_common.hpp"
 
 namespace frsg {
@@ -250,12 +252,13 @@ hipError_t launch_cfl_tri(const KParams& P, const double* Un, hipStream_t s) {
 // Each element gets 4 x SLOTS threads, thread (state s, slot): slot < N_p is
 // solution point j, slot < 3 nfp is flux point fk.  A thread keeps its own
 // chaos coefficients of state s at point j, the neighbour's modal trace at flux
-// point fk and the projection accumulators of (s, j) in registers; per random
-// node it expands both, and the element's nodal values, fluxes, traces and face
-// jumps pass through LDS.  The residual is projected on the fly and combined
-// with the stage inputs in the epilogue, so a stage reads the state once and
-// writes it once; the neighbours' modal traces come from a trace pass
-// (E x 3 nfp x S x M doubles) over the stage input.
+// point fk and the projection accumulators of (s, j) in registers; per group of
+// four random nodes it expands both, and the element's nodal values, fluxes,
+// traces and interactive fluxes pass through LDS (k_stage_tri).  The residual is
+// projected on the fly and combined with the stage inputs in the epilogue, so a
+// stage reads the state once and writes it once; the neighbours' modal traces
+// (E x 3 nfp x S x M doubles) were written by the launch that wrote the stage
+// input, or by a trace pass (k_limit_tri) before the first.
 namespace {
 
 template <int PD>

@@ -257,8 +257,9 @@ k_stage2w(KParams P, StageArgs A, const double* __restrict__ PhiT, const double*
   using H2 = Half2<double>;
   // The loop's LDS.  sU: nodal values of an element at the group's nodes, [row][variable pair]
   // [point]; the interface fluxes take its place (written and read by the element's own wave).
-  // sT: traces at the faces inside the tile, for the neighbour, by group parity: slots x-lo,
-  // x-hi and the tile's inner y face.  sH: traces of the elements around the tile at every node.
+  // sT: traces at the faces inside the tile, for the neighbour, [row][variable
+  // pair][direction: the tile's inner x or y face][face point]; one buffer, which the barrier at the
+  // end of a group keeps until the neighbour has read it.  sH: traces of the elements around the tile at every node.
   struct LoopLds {
     H2 sU[WE][4][2][NSP];
     H2 sT[WE][4][2][2][NP];
@@ -422,7 +423,7 @@ k_stage2w(KParams P, StageArgs A, const double* __restrict__ PhiT, const double*
     else nbr_halo = 2 * WY + WX + lx;
   }
   const bool wave_at_boundary = __ballot(boundary) != 0;
-  // where the lane reads the neighbour's trace: in sT (with the group's parity) or in sH
+  // where the lane reads the neighbour's trace: in sT or in sH
   const bool inner = nbr_le >= 0;
   const H2* const nb_base = inner ? &sT[nbr_le][h][0][fside >> 1][fi]
                                   : reinterpret_cast<const H2*>(&sH[0][nbr_halo][fi]);

@@ -67,7 +67,11 @@ struct Op {
 // its remainder, which rounds like the division (three operations beside the shared reciprocal
 // instead of a dozen).  So the Euler equations in FP64 round as in the stage kernel: where the
 // limiter has set a pressure to its floor, the next stage's test on it is a tie that the last bit
-// decides.  (The FP32-mixed loop keeps the divisions of the stage kernel.)
+// decides.  (The FP32-mixed loop keeps the divisions of the stage kernel.)  It holds for
+// normal numbers.  A divisor of zero, or a numerator or quotient that overflows, gives NaN where
+// the division gives an infinity: a density of zero fails the limiter's density test, a mean is refused
+// and a wave speed counts as infinite either way; only a nodal momentum whose square overflows
+// (above 1e154) passes the pressure test as NaN, which minus infinity would fail.
 struct Quotient {
   double r, d;
   __device__ __forceinline__ explicit Quotient(double x) : r(recip(x)), d(x) {}
