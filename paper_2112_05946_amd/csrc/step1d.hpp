@@ -27,7 +27,7 @@
 // the same step with one launch per stage: both give the same bits.
 //
 // Measured (FP64, per step, against one launch per stage): Burgers 1024 elements 24.1 -> 13.7 us,
-// Sod 2048 elements 50 -> 32.3, Sod with HLL and Bogacki-Shampine, 1501 elements, 57 -> 33.4, one
+// Sod 2048 elements 50 -> 33, Sod with HLL and Bogacki-Shampine, 1501 elements, 57 -> 34, one
 // RK4 step of the 64-element wave problem 32.8 -> 15.8; 64-element advection, every step in one
 // launch, 13.4 -> 6.9.  What is left is latency: a wave alone on its SIMD issues an FP64
 // instruction every 8 cycles or so, which is why a thread holds one node (two nodes per thread
